@@ -81,6 +81,55 @@ def test_arpls_matches_oracle(dev, nb, nsub, F, lam, ratio, itermax):
     assert (po >= 1).all() and (po <= itermax).all()
 
 
+def _arpls_banded(y, lam, ratio, itermax):
+    """ArPLS of one spectrum with LAPACK's banded Cholesky (the oracle's steps; its dense solve
+    is too slow for thousands of channels)."""
+    from scipy.linalg import solveh_banded
+    F = y.size
+    ab = np.zeros((3, F))
+    ab[2, :F - 2] += 1.0
+    ab[2, 1:F - 1] += 4.0
+    ab[2, 2:] += 1.0
+    ab[1, 1:F - 1] -= 2.0
+    ab[1, 2:] -= 2.0
+    ab[0, 2:] += 1.0
+    w = np.ones(F)
+    for it in range(itermax):
+        a = lam * ab
+        a[2] += w
+        z = solveh_banded(a, w * y)
+        d = y - z
+        neg = d[d < 0]
+        if neg.size < 2:
+            break
+        m, s = neg.mean(), neg.std(ddof=1)
+        if not s > 0:
+            break
+        wt = 1.0 / (1.0 + np.exp(2.0 * (d - (2.0 * s - m)) / s))
+        if np.linalg.norm(w - wt) / np.linalg.norm(w) < ratio:
+            break
+        w = wt
+    return z, it + 1
+
+
+@pytest.mark.parametrize("F", [4, 5, 61, 255, 256, 257, 1023, 1024, 1025, 2047, 2049, 4095, 4096,
+                               4097, 8191, 8193, 9001])
+def test_arpls_chunk_edges(dev, F):
+    """The chunks of every kernel instance at their ends (256, 1024, 2048, 4096, 8192 channels)
+    and past the last one. Both sides solve with a backward error of a few ulps and a condition
+    number of about 16 lam / 0.5 = 3e6: agreement to 1e-8 of the spectrum's scale."""
+    rng = np.random.default_rng(F)
+    y = _spectra(rng, 2, 2, F) if F >= 40 else 100 + 5 * rng.standard_normal((2, F, 2))
+    L = np.array([1017, 2048])
+    S = np.rint(y * L[:, None, None]).astype(np.int64)
+    zg, pg = _run_arpls(dev, S, L)
+    for k in range(2):
+        for b in range(2):
+            z, n = _arpls_banded(S[k, :, b] / L[k], 1e5, 0.05, 100)
+            assert np.abs(zg[k, :, b] - z).max() <= 1e-8 * np.abs(y).max()
+            assert pg[k, b] == n
+
+
 def test_arpls_edge_cases(dev):
     rng = np.random.default_rng(5)
     # fewer than three channels: the baseline is the spectrum itself

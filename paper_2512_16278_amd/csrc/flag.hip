@@ -271,15 +271,17 @@ __device__ int cmp_sq(uint64_t M, int x, uint64_t mv, int xv) {
 }
 
 // mu = Q1 / (N 2^40), sigma = sqrt((N Q2 - Q1^2) / (N^2 2^80)), thr = mu +
-// kappa sigma, as the exact rationals rounded once each (N > 0), computed by
+// kappa sigma, as the exact rationals rounded once each (N > 0), searched by
 // the 64 lanes of one wavefront at once: lanes 0-15 place Q1 / N and lanes
 // 16-31 (N Q2 - Q1^2) / N^2 between 16 consecutive rounding midpoints around
 // their FP64 estimates in one round of exact comparisons, then lanes 0-15 do
 // the same for the square root. A quotient whose 17 candidates straddle a
 // power of two (or fall outside the window) is finished by the sequential
 // search. Every lane gets the results.
-__device__ __noinline__ void fit_wave(int64_t N, u128 Q1, u128 Q2, double kappa, double& mu, double& sigma,
-                         double& thr) {
+struct Fit {
+  double mu, sigma, thr;
+};
+__device__ __noinline__ Fit fit_search(int64_t N, u128 Q1, u128 Q2, double kappa) {
 #pragma clang fp contract(off)
   const int lane = threadIdx.x & 63;
   const int grp = (lane >> 4) & 1, j = lane & 15;
@@ -321,7 +323,7 @@ __device__ __noinline__ void fit_wave(int64_t N, u128 Q1, u128 Q2, double kappa,
     if ((gtie >> cnt) & 1u) c += (c & 1);           // exactly on a midpoint: the even one
     val = ldexp((double)c, e);
   }
-  mu = ldexp(__shfl(val, 0), -40);
+  const double mu = ldexp(__shfl(val, 0), -40);
   const double var = ldexp(__shfl(val, 16), -80);
   // sigma: the correctly rounded square root of var
   double sg;
@@ -343,9 +345,91 @@ __device__ __noinline__ void fit_wave(int64_t N, u128 Q1, u128 Q2, double kappa,
     if (!in2 || c2 == 0 || c2 == 16) sg = sqrt_rn(var);
     else sg = ldexp((double)(mr + c2 - 8), xr);
   }
-  sigma = sg;
-  const double ks = kappa * sigma;     // two roundings: no fused multiply-add here
+  const double ks = kappa * sg;        // two roundings: no fused multiply-add here
+  return {mu, sg, mu + ks};
+}
+
+// A non-negative integer as (h + l) 2^e, h its leading 53 bits and l < 1 the
+// next 53: within 2^-105 of it, relative. A must not be zero.
+struct Lead {
+  double h, l;
+  int e;
+};
+__device__ __forceinline__ Lead lead106(const U320& A) {
+  const int n = bitlen(A);
+  const U320 B = shl320(A, 320 - n);                 // top bit at 319
+  const uint64_t hi = B.w[4] >> 11;                  // bits 319 .. 267
+  const uint64_t lo = ((B.w[4] & 0x7ff) << 42) | (B.w[3] >> 22);   // bits 266 .. 214
+  return {(double)hi, (double)lo * 1.1102230246251565e-16, n - 53};
+}
+
+// A / (dh + dl) to about 2^-102 relative, rounded to the nearest FP64 value
+// times 2^e; ok = false if the rounding could go either way at that accuracy
+// (the quotient is within 2^-40 ulp of a rounding boundary).
+__device__ __forceinline__ double quick_div(const Lead& A, double dh, double dl, bool& ok) {
+#pragma clang fp contract(off)
+  const double H = A.h + A.l, Lw = A.l - (H - A.h);
+  const double q1 = H / dh;
+  const double r = fma(-q1, dh, H) + fma(-q1, dl, Lw);
+  const double q2 = r / dh;
+  const double m = q1 + q2, t = fabs(q2 - (m - q1));
+  int em;
+  (void)frexp(m, &em);
+  const double u = ldexp(1.0, em - 53);              // ulp of m
+  // the boundaries: half an ulp away, or a quarter below a power of two
+  ok = ok && fabs(t - 0.5 * u) > 0x1p-40 * u && fabs(t - 0.25 * u) > 0x1p-40 * u;
+  return m;
+}
+
+// The fit from leading digits: each quotient to twice FP64's digits, which
+// settles its rounding except within 2^-40 ulp of a boundary; the square root
+// checked by its exact residual. False (nothing settled): search.
+__device__ __forceinline__ bool fit_quick(int64_t N, u128 Q1, u128 Q2, double kappa, double& mu,
+                                          double& sigma, double& thr) {
+#pragma clang fp contract(off)
+  if (N >= ((int64_t)1 << 53)) return false;
+  bool ok = true;
+  const double dN = (double)N;
+  U320 X{};
+  X.w[0] = (uint64_t)Q1;
+  X.w[1] = (uint64_t)(Q1 >> 64);
+  mu = 0.0;
+  if (Q1 != 0) {
+    const Lead a = lead106(X);
+    mu = ldexp(quick_div(a, dN, 0.0, ok), a.e - 40);
+  }
+  X = mul128x128((u128)(uint64_t)N, Q2);
+  sub320(X, mul128x128(Q1, Q1));
+  sigma = 0.0;
+  if (bitlen(X) != 0) {
+    const Lead a = lead106(X);
+    const double d2 = dN * dN;
+    const double var = ldexp(quick_div(a, d2, fma(dN, dN, -d2), ok), a.e - 80);
+    const double r = sqrt(var);
+    const double e = fma(-r, r, var);                // exact
+    int er;
+    const double fr = frexp(r, &er);
+    // |sqrt(var) - r| = |e| / (2 r) must be below half an ulp (a quarter below
+    // a power of two)
+    const double u = ldexp(fr == 0.5 && e < 0.0 ? 0.5 : 1.0, er - 53);
+    ok = ok && fabs(e) < r * u * (1.0 - 0x1p-40);
+    sigma = r;
+  }
+  const double ks = kappa * sigma;
   thr = mu + ks;
+  return ok;
+}
+
+// The exact fit, the same inputs and results in every lane of a wavefront. The
+// search costs some 7 us of dependent wide-integer steps on one wavefront, the
+// quick form well under 1 us.
+__device__ __forceinline__ void fit_wave(int64_t N, u128 Q1, u128 Q2, double kappa, double& mu,
+                                         double& sigma, double& thr) {
+  if (fit_quick(N, Q1, Q2, kappa, mu, sigma, thr)) return;
+  const Fit f = fit_search(N, Q1, Q2, kappa);    // by value: results in registers, no stack
+  mu = f.mu;
+  sigma = f.sigma;
+  thr = f.thr;
 }
 
 __device__ __forceinline__ int64_t thr_to_T(double thr) {
@@ -906,18 +990,32 @@ __global__ __launch_bounds__(kGridThreads) void clip_mask_kernel(ClipJob job0, c
 
 // ---------------------------------------------------------------------------
 // Clip scopes (Sec. 3.3: outliers are masked as a function of frequency and
-// time): one workgroup clips one segment of cells -- a channel over its
-// sub-intervals, a sub-interval over its channels, or the whole block -- with
-// the same exact iteration, re-reading its cells every pass; the masks of the
-// requested scopes are OR-ed into one. The fit is the exact moment fit, or the
-// histogram Gaussian fit: 64 bins of width sigma_m / 8 over +-4 sigma_m of
-// the exact moment fit, a least-squares parabola through the log counts with
-// weights c^2 (one thread, bins in index order, the operation order of the
-// definition, no fused multiply-add), falling back to the moments where the
-// parabola is undefined.
-constexpr int kSegThreads = 256;      // channel and sub-interval segments
+// time): a segment of cells -- a channel over its sub-intervals, a sub-interval
+// over its channels, or the whole block -- is clipped with the same exact
+// iteration; the masks of the requested scopes are OR-ed into one. The fit is
+// the exact moment fit, or the histogram Gaussian fit: 64 bins of width
+// sigma_m / 8 over +-4 sigma_m of the exact moment fit, a least-squares
+// parabola through the log counts with weights c^2 (bins in index order, the
+// operation order of the definition, no fused multiply-add), falling back to
+// the moments where the parabola is undefined.
+//
+// Who clips a segment depends on its length m (seg_iterate below is the
+// iteration of all of them):
+//  - m <= 512: one wavefront, the cells in its registers (a sum or a fit needs
+//    no barrier and no reload; four segments share a workgroup);
+//  - m <= 16384: one workgroup, the eligible cells kept in LDS;
+//  - longer: one workgroup re-reading its cells every pass, except the whole
+//    block with the histogram fit, whose two passes per fit run over many
+//    workgroups (hist_moments_kernel, hist_bins_kernel).
+// 99 x 4096 cells, histogram fit: channels (99 cells) 26 us, sub-intervals
+// (4096 cells) 49 us, whole block 190 us over all its launches (one workgroup
+// per segment and a reload per pass: 169, 148 and 1985 us).
+constexpr int kSegThreads = 256;      // four short segments, or one long one
+constexpr int kSegLdsThreads = 512;   // a segment kept in LDS
 constexpr int kSegThreadsAll = 1024;  // the whole block as one segment
 constexpr int kSegUnroll = 4;         // cells per thread whose loads are issued together
+constexpr int kSegWaveMax = 512;      // cells of a segment held by one wavefront
+constexpr int kSegLdsMax = 16384;     // cells of a segment held in LDS
 constexpr int kBins = 64;
 
 struct SegArgs {
@@ -931,42 +1029,70 @@ struct SegArgs {
   int write;             // 1: store the mask, 0: OR it in
 };
 
-// the segment's i-th cell (MODE 0: channel blockIdx.x over sub-intervals;
-// 1: sub-interval blockIdx.x over channels; 2: every cell)
+// the i-th cell of segment g (MODE 0: channel g over sub-intervals; 1:
+// sub-interval g over channels; 2: every cell)
 template <int MODE>
-__device__ __forceinline__ int64_t seg_cell(const SegArgs& a, int64_t i) {
-  if constexpr (MODE == 0) return i * a.nchan + blockIdx.x;
-  else if constexpr (MODE == 1) return (int64_t)blockIdx.x * a.nchan + i;
+__device__ __forceinline__ int64_t seg_cell(const SegArgs& a, int64_t g, int64_t i) {
+  if constexpr (MODE == 0) return i * a.nchan + g;
+  else if constexpr (MODE == 1) return g * a.nchan + i;
   else return i;
 }
+template <int MODE>
+__device__ __forceinline__ int64_t seg_len(const SegArgs& a) {
+  return MODE == 0 ? a.nsub : (MODE == 1 ? a.nchan : (int64_t)a.nsub * a.nchan);
+}
+__device__ __forceinline__ ClipJob seg_job(const SegArgs& a) {
+  return ClipJob{a.nsub, a.nchan, a.max_iter, 0, a.kappa, a.stat, a.status, a.protect,
+                 nullptr, a.mask, nullptr, nullptr, 0};
+}
 
-// mu, sigma of the histogram fit (thread 0; cnt: the 64 bin counts)
-__device__ void hist_fit(const unsigned* cnt, int64_t N, double mu_m, double sg_m, double& mu,
-                         double& sg) {
+// Scratch of one histogram fit (by one wavefront).
+struct HistScratch {
+  double term[8][kBins + 2];   // rows 2 doubles apart in the banks
+  double sum[8];
+};
+
+// Orders a wavefront's LDS accesses with those of its other lanes.
+__device__ __forceinline__ void wave_lds_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+}
+
+// mu, sigma of the histogram fit by one wavefront: lane i forms the terms of
+// bin i (c: its count), lanes 0 .. 7 add one series each in index order (an
+// empty bin adds zero), every lane gets the result.
+__device__ void hist_fit_wave(unsigned c, int64_t N, double mu_m, double sg_m, HistScratch& h,
+                              double& mu, double& sg) {
 #pragma clang fp contract(off)
+  const int lane = threadIdx.x & 63;
   mu = mu_m;
   sg = sg_m;
-  if (N < 8 || !(sg_m > 0.0)) return;
-  int nz = 0;
-  double S0 = 0.0, S1 = 0.0, S2 = 0.0, S3 = 0.0, S4 = 0.0, T0 = 0.0, T1 = 0.0, T2 = 0.0;
-  for (int i = 0; i < kBins; ++i) {
-    const unsigned c = cnt[i];
-    if (c == 0) continue;
-    ++nz;
-    const double z = ((double)i + 0.5) * 0.125 - 4.0;
-    const double y = log((double)c);
-    const double wt = (double)c * (double)c;
-    const double z2 = z * z;
-    S0 += wt;
-    S1 += wt * z;
-    S2 += wt * z2;
-    S3 += wt * (z2 * z);
-    S4 += wt * (z2 * z2);
-    T0 += wt * y;
-    T1 += wt * (z * y);
-    T2 += wt * (z2 * y);
+  const int nz = __popcll(__ballot(c != 0));
+  if (N < 8 || !(sg_m > 0.0) || nz < 3) return;
+  const double z = ((double)lane + 0.5) * 0.125 - 4.0;
+  const double y = c ? log((double)c) : 0.0;
+  const double wt = (double)c * (double)c;
+  const double z2 = z * z;
+  h.term[0][lane] = wt;
+  h.term[1][lane] = wt * z;
+  h.term[2][lane] = wt * z2;
+  h.term[3][lane] = wt * (z2 * z);
+  h.term[4][lane] = wt * (z2 * z2);
+  h.term[5][lane] = wt * y;
+  h.term[6][lane] = wt * (z * y);
+  h.term[7][lane] = wt * (z2 * y);
+  wave_lds_sync();
+  if (lane < 8) {
+    double t = 0.0;
+#pragma unroll
+    for (int i = 0; i < kBins; ++i) t += h.term[lane][i];
+    h.sum[lane] = t;
   }
-  if (nz < 3) return;
+  wave_lds_sync();
+  const double S0 = h.sum[0], S1 = h.sum[1], S2 = h.sum[2], S3 = h.sum[3], S4 = h.sum[4];
+  const double T0 = h.sum[5], T1 = h.sum[6], T2 = h.sum[7];
+  wave_lds_sync();
   const double m0 = S2 * S4 - S3 * S3;
   const double m1 = S1 * S4 - S3 * S2;
   const double m2 = S1 * S3 - S2 * S2;
@@ -983,143 +1109,527 @@ __device__ void hist_fit(const unsigned* cnt, int64_t N, double mu_m, double sg_
   sg = sg_z * sg_m;
 }
 
-template <int MODE, int NT>
-__global__ __launch_bounds__(NT) void segclip_kernel(SegArgs a) {
-  __shared__ Red3<NT> red;
-  __shared__ unsigned hcnt[kBins];
-  __shared__ int64_t sT;
-  __shared__ double sfit[3];
-  const int64_t m = MODE == 0 ? a.nsub : (MODE == 1 ? a.nchan : (int64_t)a.nsub * a.nchan);
-  const ClipJob J{a.nsub, a.nchan, a.max_iter, 0, a.kappa, a.stat, a.status, a.protect,
-                  nullptr, a.mask, nullptr, nullptr, 0};
-  const int64_t ncell = (int64_t)a.nsub * a.nchan;
-  if (threadIdx.x == 0) sT = INT64_MAX;
-  int64_t prevN = -1, N = 0, Nelig = -1;
-  u128 Q1 = 0, Q2 = 0;
-  int it = 0, converged = 1;
-  bool last_exact = true;
+// The bins of a fit: bin of a value, or -1 outside them.
+struct BinEdges {
+  double lo, w;
+  __device__ __forceinline__ BinEdges(double mu_m, double sg_m) {
+#pragma clang fp contract(off)
+    lo = mu_m - 4.0 * sg_m;
+    w = sg_m * 0.125;
+  }
+  __device__ __forceinline__ int of(int64_t q) const {
+#pragma clang fp contract(off)
+    const double f = floor(((double)q / TWO40 - lo) / w);
+    return f >= 0.0 && f < (double)kBins ? (int)f : -1;
+  }
+};
+
+// The iteration's state, the same in every thread of the segment.
+struct SegState {
+  int64_t T, prevN, N, Nelig;
+  double mu, sigma, thr;
+  int it, converged;
+};
+__device__ __forceinline__ SegState seg_start() {
+  return {INT64_MAX, -1, 0, -1, NAN, NAN, NAN, 0, 1};
+}
+
+// What the sums (N, Q1, Q2) at the running threshold decide: true when the
+// clip has ended (nothing new masked, the cap reached, nothing left to fit).
+__device__ __forceinline__ bool seg_done(const SegArgs& a, SegState& st, int64_t N) {
+  st.N = N;
+  if (st.Nelig < 0) st.Nelig = N;
+  if (st.it > 0 && N == st.prevN) return true;
+  if (st.it > 0 && st.it >= a.max_iter) {
+    st.converged = 0;
+    return true;
+  }
+  return N == 0;
+}
+__device__ __forceinline__ void seg_step(SegState& st, int64_t Tn) {
+  if (Tn < st.T) st.T = Tn;
+  ++st.it;
+  st.prevN = st.N;
+}
+
+// The exact clip of one segment from any state: sums(T, n, q1, q2) gives every
+// thread the exact sums over the eligible cells with q <= T, hist(T, edges,
+// N, mu_m, sg_m, mu, sg) the histogram fit of the same cells. Every thread (or
+// every lane of a one-wavefront segment) computes the same decisions.
+template <class Sums, class Hist>
+__device__ __forceinline__ void seg_iterate(const SegArgs& a, SegState& st, Sums&& sums,
+                                            Hist&& hist) {
   int64_t Nl = 0;                        // sums of the last fit
   u128 Q1l = 0, Q2l = 0;
-  double mu = NAN, sigma = NAN, thr = NAN;
-  for (int guard = 0; guard <= a.max_iter + 1; ++guard) {
-    __syncthreads();
-    const int64_t T = sT;
-    __syncthreads();
+  bool last_exact = true;
+  for (;;) {
     int64_t n = 0;
     u128 q1 = 0, q2 = 0;
+    sums(st.T, n, q1, q2);
+    if (seg_done(a, st, n)) break;
+    Nl = n; Q1l = q1; Q2l = q2;
+    int64_t Tn;
+    if (a.fit == 0) {
+      bool ok;
+      Tn = fit_T_fast(n, q1, q2, a.kappa, ok);
+      last_exact = !ok;
+      if (!ok) {
+        fit_wave(n, q1, q2, a.kappa, st.mu, st.sigma, st.thr);
+        Tn = thr_to_T(st.thr);
+      }
+    } else {
+      double mu_m, sg_m, t_;
+      fit_wave(n, q1, q2, a.kappa, mu_m, sg_m, t_);
+      hist(st.T, BinEdges(mu_m, sg_m), n, mu_m, sg_m, st.mu, st.sigma);
+      {
+#pragma clang fp contract(off)
+        const double ks = a.kappa * st.sigma;
+        st.thr = st.mu + ks;
+      }
+      Tn = thr_to_T(st.thr);
+    }
+    seg_step(st, Tn);
+  }
+  // the reported fit is the exact one, from the last fit's sums
+  if (!last_exact) fit_wave(Nl, Q1l, Q2l, a.kappa, st.mu, st.sigma, st.thr);
+}
+
+__device__ __forceinline__ void seg_report(const SegArgs& a, int64_t g, const SegState& st) {
+  if (!a.out) return;
+  rfi_flag_stats& o = a.out[g];
+  o.mu = st.mu;
+  o.sigma = st.sigma;
+  o.thr = st.thr;
+  o.iterations = st.it;
+  o.converged = st.converged;
+  o.nflag = (st.Nelig < 0 ? 0 : st.Nelig) - st.N;
+  o.nfit = st.N;
+}
+
+// Whether q fits the 64-bit split sums (acc_split).
+__device__ __forceinline__ bool fits_split(int64_t q) {
+  return (uint64_t)q < ((uint64_t)1 << 42);
+}
+
+// One wavefront per segment of at most 64 PER cells, held in registers.
+template <int MODE, int PER>
+__global__ __launch_bounds__(kSegThreads) void segclip_wave_kernel(SegArgs a) {
+  __shared__ HistScratch hs[kSegThreads / 64];
+  __shared__ unsigned hcnt[kSegThreads / 64][kBins];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int64_t g = (int64_t)blockIdx.x * (kSegThreads / 64) + wave;
+  if (g >= (MODE == 0 ? a.nchan : a.nsub)) return;      // whole wavefronts leave together
+  const ClipJob J = seg_job(a);
+  const int64_t ncell = (int64_t)a.nsub * a.nchan, m = seg_len<MODE>(a);
+  int64_t q[PER];
+  bool ok[PER];
+  {
+    CellLd x[PER];
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+      const int64_t i = lane + 64 * u;
+      x[u] = load_cell(J, seg_cell<MODE>(a, g, i < m ? i : 0), ncell);
+    }
+    bool fit = true;
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+      ok[u] = lane + 64 * u < m && elig(x[u]);
+      q[u] = quant(x[u].s);
+      fit = fit && (!ok[u] || fits_split(q[u]));
+    }
+    SegState st = seg_start();
+    const bool split = __all(fit);
+    auto sums = [&](int64_t T, int64_t& n, u128& q1, u128& q2) {
+      if (split) {
+        SplitSums t{0, 0, 0, 0, 0};
+#pragma unroll
+        for (int u = 0; u < PER; ++u)
+          if (ok[u] && q[u] <= T) acc_split(q[u], t);
+        n = (int64_t)wave_sum_u32(t.n);
+        q1 = (u128)wave_sum_u64(t.a);
+        q2 = ((u128)wave_sum_u64(t.h2) << 42) + ((u128)wave_sum_u64(t.hl) << 22) +
+             (u128)wave_sum_u64(t.l2);
+      } else {
+#pragma unroll
+        for (int u = 0; u < PER; ++u)
+          if (ok[u] && q[u] <= T) acc(q[u], n, q1, q2);
+        wave_sum3(n, q1, q2);
+      }
+    };
+    auto hist = [&](int64_t T, const BinEdges& e, int64_t N, double mu_m, double sg_m, double& mu,
+                    double& sg) {
+      hcnt[wave][lane] = 0;
+      wave_lds_sync();
+#pragma unroll
+      for (int u = 0; u < PER; ++u)
+        if (ok[u] && q[u] <= T) {
+          const int b = e.of(q[u]);
+          if (b >= 0) atomicAdd(&hcnt[wave][b], 1u);
+        }
+      wave_lds_sync();
+      hist_fit_wave(hcnt[wave][lane], N, mu_m, sg_m, hs[wave], mu, sg);
+    };
+    seg_iterate(a, st, sums, hist);
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+      if (lane + 64 * u >= m) continue;
+      const int64_t c = seg_cell<MODE>(a, g, lane + 64 * u);
+      const bool hit = ok[u] && q[u] > st.T;
+      if (a.write) a.mask[c] = hit ? 1 : 0;
+      else if (hit) a.mask[c] = 1;
+    }
+    if (lane == 0) seg_report(a, g, st);
+  }
+}
+
+// Histogram fit of a segment owned by one workgroup: count(e, bins) adds the
+// live cells into the wave's bins; wave 0 fits, the others read its result.
+template <int NT>
+struct BlockHist {
+  HistScratch hs;
+  unsigned bins[NT / 64][kBins];
+  double fit[2];
+};
+template <int NT, class Count>
+__device__ __forceinline__ void block_hist(BlockHist<NT>& h, const BinEdges& e, int64_t N,
+                                           double mu_m, double sg_m, double& mu, double& sg,
+                                           Count&& count) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  h.bins[wave][lane] = 0;
+  wave_lds_sync();                       // only this wave adds to them
+  count(e, h.bins[wave]);
+  __syncthreads();
+  if (wave == 0) {
+    unsigned c = 0;
+#pragma unroll
+    for (int w = 0; w < NT / 64; ++w) c += h.bins[w][lane];
+    double m_, s_;
+    hist_fit_wave(c, N, mu_m, sg_m, h.hs, m_, s_);
+    if (lane == 0) {
+      h.fit[0] = m_;
+      h.fit[1] = s_;
+    }
+  }
+  __syncthreads();
+  mu = h.fit[0];
+  sg = h.fit[1];
+}
+
+// One workgroup per segment of at most kSegLdsMax cells; the eligible ones are
+// compacted into LDS (their order does not matter: the sums are exact).
+template <int MODE>
+__global__ __launch_bounds__(kSegLdsThreads) void segclip_lds_kernel(SegArgs a) {
+  constexpr int NT = kSegLdsThreads;
+  extern __shared__ int64_t sq[];
+  __shared__ union {
+    Red3<NT> r3;
+    RedSplit<NT> rs;
+  } red;
+  __shared__ BlockHist<NT> bh;
+  __shared__ int live;
+  const int lane = threadIdx.x & 63;
+  const int64_t g = blockIdx.x;
+  const ClipJob J = seg_job(a);
+  const int64_t ncell = (int64_t)a.nsub * a.nchan;
+  const int m = (int)seg_len<MODE>(a);
+  if (threadIdx.x == 0) live = 0;
+  __syncthreads();
+  bool fit = true;
+  for (int i0 = threadIdx.x; i0 - lane < m; i0 += NT * kSegUnroll) {
+    CellLd x[kSegUnroll];
+#pragma unroll
+    for (int u = 0; u < kSegUnroll; ++u) {
+      const int i = i0 + u * NT;
+      x[u] = load_cell(J, seg_cell<MODE>(a, g, i < m ? i : 0), ncell);
+    }
+#pragma unroll
+    for (int u = 0; u < kSegUnroll; ++u) {
+      const bool ok = i0 + u * NT < m && elig(x[u]);
+      const int64_t q = quant(x[u].s);
+      const unsigned long long b = __ballot(ok);
+      int base = 0;
+      if (lane == 0 && b) base = atomicAdd(&live, __popcll(b));
+      base = __builtin_amdgcn_readfirstlane(base);
+      if (ok) {
+        sq[base + __popcll(b & ((1ull << lane) - 1))] = q;
+        fit = fit && fits_split(q);
+      }
+    }
+  }
+  const bool split = __syncthreads_and(fit);
+  const int M = live;
+  auto sums = [&](int64_t T, int64_t& n, u128& q1, u128& q2) {
+    if (split) {
+      SplitSums t{0, 0, 0, 0, 0};
+      for (int k = threadIdx.x; k < M; k += NT) {
+        const int64_t q = sq[k];
+        if (q <= T) acc_split(q, t);
+      }
+      block_sum_split<NT>(t, n, q1, q2, red.rs);
+    } else {
+      for (int k = threadIdx.x; k < M; k += NT) {
+        const int64_t q = sq[k];
+        if (q <= T) acc(q, n, q1, q2);
+      }
+      block_sum3<NT>(n, q1, q2, red.r3);
+    }
+  };
+  auto hist = [&](int64_t T, const BinEdges& e, int64_t N, double mu_m, double sg_m, double& mu,
+                  double& sg) {
+    block_hist<NT>(bh, e, N, mu_m, sg_m, mu, sg, [&](const BinEdges& ed, unsigned* bins) {
+      for (int k = threadIdx.x; k < M; k += NT) {
+        const int64_t q = sq[k];
+        if (q > T) continue;
+        const int b = ed.of(q);
+        if (b >= 0) atomicAdd(&bins[b], 1u);
+      }
+    });
+  };
+  SegState st = seg_start();
+  seg_iterate(a, st, sums, hist);
+  for (int i = threadIdx.x; i < m; i += NT) {
+    const int64_t c = seg_cell<MODE>(a, g, i);
+    const CellLd x = load_cell(J, c, ncell);
+    const uint8_t hit = (elig(x) && quant(x.s) > st.T) ? 1 : 0;
+    if (a.write) a.mask[c] = hit;
+    else if (hit) a.mask[c] = 1;
+  }
+  if (threadIdx.x == 0) seg_report(a, g, st);
+}
+
+// The whole block's histogram clip over many workgroups. Fit f takes two
+// launches: hist_moments_kernel (every workgroup first forms the threshold of
+// fit f - 1 from its bins, then its cells' exact sums) and hist_bins_kernel
+// (every workgroup adds up the sums, forms the moment fit and counts its cells
+// into the bins). What all workgroups need they compute redundantly, so the
+// kernel boundary is the only ordering: a last workgroup that forms the fit
+// behind device-wide fences took 30 us a launch). The host queues kHistFits fits (each returns at once when the clip has ended), then
+// segclip_kernel takes over whatever is left and reports. The state lives in
+// the first bytes of the mask, which the last two launches overwrite (the
+// call takes no other scratch).
+constexpr int kHistWG = 288;
+constexpr int kHistPer = 6;           // cells per thread and step
+constexpr int kHistFits = 10;
+constexpr int64_t kHistStep = (int64_t)kGridThreads * kHistPer;
+struct HistCtl {
+  int64_t T;                          // final threshold for the mask pass
+  SegState begin[kHistFits];          // before fit f (its threshold decided)
+  struct {
+    SegState st;                      // after the sums of fit f
+    double mu_m, sg_m;
+    int done;                         // 0: the bins follow; 1: the clip ended here;
+                                      // 2: not reached
+  } fit[kHistFits];
+  unsigned bins[kHistFits][kBins];
+  struct {
+    uint32_t n, q1hi;                 // at most 2^30 cells: q1 < 2^94
+    uint64_t q1lo, q2[2];
+  } part[kHistWG];
+};
+static_assert(sizeof(HistCtl) + 64 <= kSegLdsMax, "the mask of a longer block holds the state");
+
+__global__ __launch_bounds__(256) void hist_init_kernel(HistCtl* ct) {
+  for (int i = threadIdx.x; i < kHistFits * kBins; i += 256) ct->bins[i / kBins][i % kBins] = 0;
+  if (threadIdx.x < kHistFits) ct->fit[threadIdx.x].done = 2;
+}
+
+// the threshold of a fit from its bins (one wavefront)
+__device__ __forceinline__ SegState hist_step(const SegArgs& a, const HistCtl* ct, int f,
+                                              HistScratch& hs) {
+  SegState st = ct->fit[f].st;
+  hist_fit_wave(ct->bins[f][threadIdx.x & 63], st.N, ct->fit[f].mu_m, ct->fit[f].sg_m, hs, st.mu,
+                st.sigma);
+  {
+#pragma clang fp contract(off)
+    const double ks = a.kappa * st.sigma;
+    st.thr = st.mu + ks;
+  }
+  seg_step(st, thr_to_T(st.thr));
+  return st;
+}
+
+template <class F>
+__device__ __forceinline__ void hist_cells(const SegArgs& a, F&& f) {
+  const ClipJob J = seg_job(a);
+  const int64_t ncell = (int64_t)a.nsub * a.nchan;
+  for (int64_t c0 = blockIdx.x * kHistStep; c0 < ncell; c0 += gridDim.x * kHistStep) {
+    CellLd x[kHistPer];
+#pragma unroll
+    for (int u = 0; u < kHistPer; ++u)
+      x[u] = load_cell(J, c0 + u * kGridThreads + threadIdx.x, ncell);
+#pragma unroll
+    for (int u = 0; u < kHistPer; ++u)
+      if (c0 + u * kGridThreads + threadIdx.x < ncell && elig(x[u])) f(quant(x[u].s));
+  }
+}
+
+__global__ __launch_bounds__(kGridThreads) void hist_moments_kernel(SegArgs a, HistCtl* ct,
+                                                                    int f) {
+  __shared__ Red3<kGridThreads> red;
+  __shared__ HistScratch hs;
+  __shared__ int64_t sT;
+  if (f > 0 && ct->fit[f - 1].done) return;
+  if (threadIdx.x < 64) {
+    const SegState st = f > 0 ? hist_step(a, ct, f - 1, hs) : seg_start();
+    if (threadIdx.x == 0) {
+      sT = st.T;
+      if (blockIdx.x == 0) ct->begin[f] = st;
+    }
+  }
+  __syncthreads();
+  const int64_t T = sT;
+  int64_t n = 0;
+  u128 q1 = 0, q2 = 0;
+  hist_cells(a, [&](int64_t q) {
+    if (q <= T) acc(q, n, q1, q2);
+  });
+  block_sum3<kGridThreads>(n, q1, q2, red);
+  if (threadIdx.x == 0) {
+    auto& p = ct->part[blockIdx.x];
+    p.n = (uint32_t)n;
+    p.q1hi = (uint32_t)(q1 >> 64);
+    p.q1lo = (uint64_t)q1;
+    p.q2[0] = (uint64_t)q2;
+    p.q2[1] = (uint64_t)(q2 >> 64);
+  }
+}
+
+__global__ __launch_bounds__(kGridThreads) void hist_bins_kernel(SegArgs a, HistCtl* ct, int f) {
+  __shared__ Red3<kGridThreads> red;
+  __shared__ unsigned bins[kGridThreads / 64][kBins];
+  if (f > 0 && ct->fit[f - 1].done) return;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  int64_t n = 0;
+  u128 q1 = 0, q2 = 0;
+  for (int w = threadIdx.x; w < (int)gridDim.x; w += kGridThreads) {
+    const auto p = ct->part[w];
+    n += p.n;
+    q1 += mk128(p.q1lo, p.q1hi);
+    q2 += mk128(p.q2[0], p.q2[1]);
+  }
+  SegState st = ct->begin[f];
+  block_sum3<kGridThreads>(n, q1, q2, red);
+  const bool done = seg_done(a, st, n);
+  double mu_m = 0.0, sg_m = 0.0, t_;
+  if (!done) fit_wave(n, q1, q2, a.kappa, mu_m, sg_m, t_);
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    ct->fit[f].st = st;
+    ct->fit[f].mu_m = mu_m;
+    ct->fit[f].sg_m = sg_m;
+    ct->fit[f].done = done;
+  }
+  if (done) return;
+  const BinEdges e(mu_m, sg_m);
+  bins[wave][lane] = 0;
+  wave_lds_sync();
+  hist_cells(a, [&](int64_t q) {
+    if (q > st.T) return;
+    const int b = e.of(q);
+    if (b >= 0) atomicAdd(&bins[wave][b], 1u);
+  });
+  __syncthreads();
+  if (wave == 0) {
+    unsigned c = 0;
+#pragma unroll
+    for (int w = 0; w < kGridThreads / 64; ++w) c += bins[w][lane];
+    if (c) atomicAdd(&ct->bins[f][lane], c);
+  }
+}
+
+// Cells outside [c0, c1) (all workgroups), or those inside it (inside = 1, one
+// workgroup): the mask bytes of that range hold the threshold until then.
+template <int NT>
+__global__ __launch_bounds__(NT) void hist_mask_kernel(SegArgs a, const HistCtl* ct, int64_t c0,
+                                                       int64_t c1, int inside) {
+  const ClipJob J = seg_job(a);
+  const int64_t ncell = (int64_t)a.nsub * a.nchan;
+  const int64_t T = ct->T;
+  __syncthreads();                       // inside: every thread has read T
+  const int64_t lo = inside ? c0 : 0, hi = inside ? c1 : ncell;
+  constexpr int64_t step = (int64_t)NT * kChunkPer;
+  for (int64_t b0 = lo + (int64_t)blockIdx.x * step; b0 < hi; b0 += (int64_t)gridDim.x * step) {
+    CellLd x[kChunkPer];
+#pragma unroll
+    for (int u = 0; u < kChunkPer; ++u) x[u] = load_cell(J, b0 + u * NT + threadIdx.x, ncell);
+#pragma unroll
+    for (int u = 0; u < kChunkPer; ++u) {
+      const int64_t c = b0 + u * NT + threadIdx.x;
+      if (c < hi && (inside || c < c0 || c >= c1))
+        a.mask[c] = (elig(x[u]) && quant(x[u].s) > T) ? 1 : 0;
+    }
+  }
+}
+
+// One workgroup per segment, re-reading its cells every pass; ct (nullable):
+// the nfit fits to go on from, and no mask (hist_mask_kernel writes it).
+template <int MODE, int NT>
+__global__ __launch_bounds__(NT) void segclip_kernel(SegArgs a, HistCtl* ct, int nfit) {
+  __shared__ Red3<NT> red;
+  __shared__ BlockHist<NT> bh;
+  const int64_t g = blockIdx.x;
+  const int64_t m = seg_len<MODE>(a);
+  const ClipJob J = seg_job(a);
+  const int64_t ncell = (int64_t)a.nsub * a.nchan;
+  auto cells = [&](auto&& f) {
     for (int64_t i0 = threadIdx.x; i0 < m; i0 += (int64_t)NT * kSegUnroll) {
       CellLd x[kSegUnroll];
 #pragma unroll
       for (int u = 0; u < kSegUnroll; ++u) {
         const int64_t i = i0 + (int64_t)u * NT;
-        x[u] = load_cell(J, seg_cell<MODE>(a, i < m ? i : 0), ncell);
+        x[u] = load_cell(J, seg_cell<MODE>(a, g, i < m ? i : 0), ncell);
       }
 #pragma unroll
-      for (int u = 0; u < kSegUnroll; ++u) {
-        if (i0 + (int64_t)u * NT >= m || !elig(x[u])) continue;
-        const int64_t q = quant(x[u].s);
-        if (q <= T) acc(q, n, q1, q2);
-      }
+      for (int u = 0; u < kSegUnroll; ++u)
+        if (i0 + (int64_t)u * NT < m && elig(x[u])) f(quant(x[u].s));
     }
+  };
+  auto sums = [&](int64_t T, int64_t& n, u128& q1, u128& q2) {
+    cells([&](int64_t q) {
+      if (q <= T) acc(q, n, q1, q2);
+    });
     block_sum3<NT>(n, q1, q2, red);
-    N = n; Q1 = q1; Q2 = q2;
-    if (Nelig < 0) Nelig = N;
-    if (it > 0 && N == prevN) break;
-    if (it > 0 && it >= a.max_iter) { converged = 0; break; }
-    if (N == 0) break;
-    Nl = N; Q1l = Q1; Q2l = Q2;
-    int64_t Tn;
-    if (a.fit == 0) {
-      bool ok;
-      Tn = fit_T_fast(N, Q1, Q2, a.kappa, ok);
-      last_exact = !ok;
-      if (!ok) {
-        if (threadIdx.x < 64) {
-          double m_, s_, t_;
-          fit_wave(N, Q1, Q2, a.kappa, m_, s_, t_);
-          if (threadIdx.x == 0) { sfit[0] = m_; sfit[1] = s_; sfit[2] = t_; }
-        }
-        __syncthreads();
-        mu = sfit[0]; sigma = sfit[1]; thr = sfit[2];
-        Tn = thr_to_T(thr);
-      }
+  };
+  auto hist = [&](int64_t T, const BinEdges& e, int64_t N, double mu_m, double sg_m, double& mu,
+                  double& sg) {
+    block_hist<NT>(bh, e, N, mu_m, sg_m, mu, sg, [&](const BinEdges& ed, unsigned* bins) {
+      cells([&](int64_t q) {
+        if (q > T) return;
+        const int b = ed.of(q);
+        if (b >= 0) atomicAdd(&bins[b], 1u);
+      });
+    });
+  };
+  SegState st = seg_start();
+  bool done = false;
+  if (ct) {
+    int f = nfit - 1;
+    while (f > 0 && ct->fit[f].done == 2) --f;
+    done = ct->fit[f].done == 1;
+    if (done) {
+      st = ct->fit[f].st;
     } else {
-      // histogram fit: exact moments, the 64 bin counts of the live values, the parabola
+      // the bins of the last fit are still to be used
+      __shared__ SegState sst;
       if (threadIdx.x < 64) {
-        double m_, s_, t_;
-        fit_wave(N, Q1, Q2, a.kappa, m_, s_, t_);
-        if (threadIdx.x == 0) { sfit[0] = m_; sfit[1] = s_; }
-      }
-      for (int i = threadIdx.x; i < kBins; i += NT) hcnt[i] = 0;
-      __syncthreads();
-      const double mu_m = sfit[0], sg_m = sfit[1];
-      {
-#pragma clang fp contract(off)
-        const double lo = mu_m - 4.0 * sg_m;
-        const double w = sg_m * 0.125;
-        for (int64_t i0 = threadIdx.x; i0 < m; i0 += (int64_t)NT * kSegUnroll) {
-          CellLd x[kSegUnroll];
-#pragma unroll
-          for (int u = 0; u < kSegUnroll; ++u) {
-            const int64_t i = i0 + (int64_t)u * NT;
-            x[u] = load_cell(J, seg_cell<MODE>(a, i < m ? i : 0), ncell);
-          }
-#pragma unroll
-          for (int u = 0; u < kSegUnroll; ++u) {
-            if (i0 + (int64_t)u * NT >= m || !elig(x[u])) continue;
-            const int64_t q = quant(x[u].s);
-            if (q > T) continue;
-            const double v = (double)q / TWO40;
-            const double f = floor((v - lo) / w);
-            if (f >= 0.0 && f < (double)kBins) atomicAdd(&hcnt[(int)f], 1u);
-          }
-        }
+        const SegState s0 = hist_step(a, ct, f, bh.hs);
+        if (threadIdx.x == 0) sst = s0;
       }
       __syncthreads();
-      if (threadIdx.x == 0) {
-#pragma clang fp contract(off)
-        double hm, hs;
-        hist_fit(hcnt, N, mu_m, sg_m, hm, hs);
-        const double ks = a.kappa * hs;
-        sfit[0] = hm; sfit[1] = hs; sfit[2] = hm + ks;
-      }
-      __syncthreads();
-      mu = sfit[0]; sigma = sfit[1]; thr = sfit[2];
-      Tn = thr_to_T(thr);
-      last_exact = true;
+      st = sst;
     }
-    if (threadIdx.x == 0 && Tn < sT) sT = Tn;
-    ++it;
-    prevN = N;
   }
-  if (a.fit == 0 && it > 0 && !last_exact) {
-    // the reported fit is the exact one, from the last fit's sums
-    if (threadIdx.x < 64) {
-      double m_, s_, t_;
-      fit_wave(Nl, Q1l, Q2l, a.kappa, m_, s_, t_);
-      if (threadIdx.x == 0) { sfit[0] = m_; sfit[1] = s_; sfit[2] = t_; }
-    }
-    __syncthreads();
-    mu = sfit[0]; sigma = sfit[1]; thr = sfit[2];
+  if (!done) seg_iterate(a, st, sums, hist);
+  if (threadIdx.x == 0) {
+    seg_report(a, g, st);
+    if (ct) ct->T = st.T;
   }
-  __syncthreads();
-  const int64_t T = sT;
+  if (ct) return;
   for (int64_t i = threadIdx.x; i < m; i += NT) {
-    const int64_t c = seg_cell<MODE>(a, i);
+    const int64_t c = seg_cell<MODE>(a, g, i);
     const CellLd x = load_cell(J, c, ncell);
-    const uint8_t hit = (elig(x) && quant(x.s) > T) ? 1 : 0;
+    const uint8_t hit = (elig(x) && quant(x.s) > st.T) ? 1 : 0;
     if (a.write) a.mask[c] = hit;
     else if (hit) a.mask[c] = 1;
-  }
-  if (threadIdx.x == 0 && a.out) {
-    rfi_flag_stats& o = a.out[blockIdx.x];
-    o.mu = mu;
-    o.sigma = sigma;
-    o.thr = thr;
-    o.iterations = it;
-    o.converged = converged;
-    o.nflag = (Nelig < 0 ? 0 : Nelig) - N;
-    o.nfit = N;
   }
 }
 
@@ -1342,35 +1852,102 @@ hipError_t launch_clip_batch(const ClipJob* jobs, const ClipJob* host_jobs, int 
   return hipGetLastError();
 }
 
+namespace {
+
+template <int MODE>
+hipError_t launch_lds(const SegArgs& a, int64_t nseg, int m, hipStream_t s) {
+  const auto kern = segclip_lds_kernel<MODE>;
+  hipError_t e = hipFuncSetAttribute((const void*)kern,
+                                     hipFuncAttributeMaxDynamicSharedMemorySize, kSegLdsMax * 8);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(kern, dim3((unsigned)nseg), dim3(kSegLdsThreads), m * 8, s, a);
+  return hipGetLastError();
+}
+
+// one clip per channel (MODE 0) or per sub-interval (1): who clips a segment
+// follows from its length (see the comment above SegArgs)
+template <int MODE>
+hipError_t launch_segments(const SegArgs& a, hipStream_t s) {
+  const int64_t m = MODE == 0 ? a.nsub : a.nchan;
+  const int64_t nseg = MODE == 0 ? a.nchan : a.nsub;
+  constexpr int kPer = kSegThreads / 64;
+  const dim3 waves((unsigned)((nseg + kPer - 1) / kPer));
+  if (m <= 128) {
+    hipLaunchKernelGGL((segclip_wave_kernel<MODE, 2>), waves, dim3(kSegThreads), 0, s, a);
+  } else if (m <= kSegWaveMax) {
+    hipLaunchKernelGGL((segclip_wave_kernel<MODE, kSegWaveMax / 64>), waves, dim3(kSegThreads), 0,
+                       s, a);
+  } else if (m <= kSegLdsMax) {
+    return launch_lds<MODE>(a, nseg, (int)m, s);
+  } else {
+    hipLaunchKernelGGL((segclip_kernel<MODE, kSegThreads>), dim3((unsigned)nseg),
+                       dim3(kSegThreads), 0, s, a, (HistCtl*)nullptr, 0);
+  }
+  return hipGetLastError();
+}
+
+bool overlap(const void* a, size_t na, const void* b, size_t nb) {
+  const uintptr_t x = (uintptr_t)a, y = (uintptr_t)b;
+  return b && x < y + nb && y < x + na;
+}
+
+// the whole block's clip with the histogram fit
+hipError_t launch_hist_all(const SegArgs& a, hipStream_t s) {
+  const int64_t ncell = (int64_t)a.nsub * a.nchan;
+  if (ncell > 0 && ncell <= kSegLdsMax) return launch_lds<2>(a, 1, (int)ncell, s);
+  // a mask that shares bytes with an input or the summary cannot hold the state
+  if (ncell == 0 || overlap(a.mask, ncell, a.stat, ncell * 8) ||
+      overlap(a.mask, ncell, a.status, ncell) || overlap(a.mask, ncell, a.protect, a.nchan) ||
+      overlap(a.mask, ncell, a.out, sizeof(rfi_flag_stats))) {
+    hipLaunchKernelGGL((segclip_kernel<2, kSegThreadsAll>), dim3(1), dim3(kSegThreadsAll), 0, s,
+                       a, (HistCtl*)nullptr, 0);
+    return hipGetLastError();
+  }
+  const int64_t c0 = (int64_t)((64 - (uintptr_t)a.mask % 64) % 64);
+  const int64_t c1 = c0 + 64;          // the mask bytes that hold the threshold
+  HistCtl* ct = (HistCtl*)(a.mask + c0);
+  const unsigned grid = (unsigned)std::min<int64_t>((ncell + kHistStep - 1) / kHistStep, kHistWG);
+  // a clip of max_iter fits needs max_iter + 1 moment passes
+  const int nfit = std::min(kHistFits, a.max_iter + 1);
+  hipLaunchKernelGGL(hist_init_kernel, dim3(1), dim3(256), 0, s, ct);
+  for (int f = 0; f < nfit; ++f) {
+    hipLaunchKernelGGL(hist_moments_kernel, dim3(grid), dim3(kGridThreads), 0, s, a, ct, f);
+    hipLaunchKernelGGL(hist_bins_kernel, dim3(grid), dim3(kGridThreads), 0, s, a, ct, f);
+  }
+  hipLaunchKernelGGL((segclip_kernel<2, kSegThreadsAll>), dim3(1), dim3(kSegThreadsAll), 0, s, a,
+                     ct, nfit);
+  hipLaunchKernelGGL((hist_mask_kernel<kGridThreads>), dim3(grid), dim3(kGridThreads), 0, s, a,
+                     (const HistCtl*)ct, c0, c1, 0);
+  hipLaunchKernelGGL((hist_mask_kernel<64>), dim3(1), dim3(64), 0, s, a, (const HistCtl*)ct,
+                     c0, c1, 1);
+  return hipGetLastError();
+}
+
+}  // namespace
+
 hipError_t launch_clip_scoped(const ClipJob& g, int scopes, int fit, rfi_flag_stats* chan_out,
                               rfi_flag_stats* sub_out, hipStream_t s) {
   const int64_t ncell = (int64_t)g.nsub * g.nchan;
   SegArgs a{g.nsub, g.nchan, g.max_iter, fit, g.kappa, g.stat, g.status, g.protect, g.mask,
             nullptr, 0};
+  hipError_t e = hipSuccess;
   if (scopes & 1) {
-    if (fit == 0) {
-      hipError_t e = launch_clip(g, s);
-      if (e != hipSuccess) return e;
-    } else {
-      a.out = g.out;
-      a.write = 1;
-      hipLaunchKernelGGL((segclip_kernel<2, kSegThreadsAll>), dim3(1), dim3(kSegThreadsAll), 0, s,
-                         a);
-    }
+    a.out = g.out;
+    a.write = 1;
+    e = fit == 0 ? launch_clip(g, s) : launch_hist_all(a, s);
   } else if (ncell > 0) {
     const unsigned grid = (unsigned)std::min<int64_t>((ncell + 255) / 256, 4096);
     hipLaunchKernelGGL(fill_u8_kernel, dim3(grid), dim3(256), 0, s, g.mask, ncell);
   }
+  if (e != hipSuccess) return e;
   a.write = 0;
   if ((scopes & 2) && g.nsub > 0) {
     a.out = chan_out;
-    hipLaunchKernelGGL((segclip_kernel<0, kSegThreads>), dim3((unsigned)g.nchan), dim3(kSegThreads),
-                       0, s, a);
+    if ((e = launch_segments<0>(a, s)) != hipSuccess) return e;
   }
   if ((scopes & 4) && g.nsub > 0) {
     a.out = sub_out;
-    hipLaunchKernelGGL((segclip_kernel<1, kSegThreads>), dim3((unsigned)g.nsub), dim3(kSegThreads),
-                       0, s, a);
+    if ((e = launch_segments<1>(a, s)) != hipSuccess) return e;
   }
   return hipGetLastError();
 }

@@ -97,3 +97,41 @@ def test_scopes_match_oracle(dev, K, F, fit):
     ref_g = clip.clip_scoped(s, elig, 3.0, 50, 1, fit).mask
     ref_u = clip.clip_scoped(s, elig, 3.0, 50, 7, fit).mask
     assert ref_u.sum() >= ref_g.sum()
+
+
+@pytest.mark.parametrize("fit", ["moments", "histogram"])
+@pytest.mark.parametrize("K,F", [(4, 5), (128, 9), (129, 64), (512, 31), (513, 33), (5, 512),
+                                 (4, 4096), (4, 16384), (4, 16387)])
+def test_scopes_segment_lengths(dev, K, F, fit):
+    """Segment lengths at the ends of each way of clipping one (128 and 512 cells in registers,
+    16384 in LDS, longer ones re-read; the whole block in LDS or over many workgroups), with a
+    mask at an odd address, against the oracle; then the histogram clip capped at one fit."""
+    import torch
+    from paper_2512_16278_amd import rfi
+    rng = np.random.default_rng(K * 31 + F)
+    s = _stat(rng, K, F)
+    status = np.zeros((K, F), np.uint8)
+    status.ravel()[rng.choice(K * F, 3, replace=False)] = rfi.RFI_CELL_DEGENERATE
+    elig = status == 0
+    st = torch.from_numpy(s.ravel().copy()).to(dev)
+    stt = torch.from_numpy(status.ravel().copy()).to(dev)
+    fcode = rfi.RFI_FIT_MOMENTS if fit == "moments" else rfi.RFI_FIT_HISTOGRAM
+    for scopes, max_iter in ((7, 50), (1, 1)):
+        mask = torch.full((K * F + 3,), 9, dtype=torch.uint8, device=dev)
+        out = torch.zeros(48, dtype=torch.uint8, device=dev)
+        co = torch.zeros(48 * F, dtype=torch.uint8, device=dev)
+        so = torch.zeros(48 * K, dtype=torch.uint8, device=dev)
+        say("segments", K, F, fit, scopes)
+        rfi.rfi_flag_scoped(K, F, st, stt, mask[3:], scopes=scopes, fit=fcode, max_iter=max_iter,
+                            out=out, chan_out=co, sub_out=so)
+        torch.cuda.synchronize()
+        ref = clip.clip_scoped(s, elig, 3.0, max_iter, scopes, fit)
+        assert (mask[:3] == 9).all()
+        assert np.array_equal(mask[3:].cpu().numpy().reshape(K, F).astype(bool), ref.mask)
+        exact = fit == "moments"
+        _cmp(_stats(out, 1)[0], ref.glob, exact)
+        if scopes == 7:
+            for j, g in enumerate(_stats(co, F)):
+                _cmp(g, ref.chan[j], exact)
+            for k, g in enumerate(_stats(so, K)):
+                _cmp(g, ref.sub[k], exact)

@@ -259,7 +259,9 @@ void fill_descriptors(const rfi_batch_item* items, BatchPlan* bpn, char* ws) {
                   nullptr, it.stat, it.v1, it.status, ip.ncell,
                   ip.solver == RFI_EIG_TRIDIAG ? 1 : 0};
       c0[cpos++] = cell;
-      cell += ip.ncell;
+      cell += ip.solver == RFI_EIG_TRIDIAG
+                  ? (ip.ncell + kTriCellPad - 1) / kTriCellPad * kTriCellPad
+                  : ip.ncell;
     }
     c0[cpos++] = cell;      // total of the class
   }
@@ -309,7 +311,7 @@ hipError_t enqueue_eig(const BatchPlan& bpn, const void* desc, char* ws, hipStre
       e = launch_eig_lane_batch(ec.lane_cls, ea + pos, c0 + cpos, m, total, s, ec.wg,
                                 ec.solver == RFI_EIG_LANE_TRI);
     else if (ec.solver == RFI_EIG_TRIDIAG)
-      e = launch_eig_tri_batch(ec.lane_cls, ea + pos, c0 + cpos, m, total, s, ec.v1);
+      e = launch_eig_tri_batch(ec.lane_cls, ea + pos, c0 + cpos, m, total, s);
     else
       e = launch_eig_wave_batch(ec.precision, ec.max_nbeam, ea + pos, c0 + cpos, m, total, s);
     if (e != hipSuccess) return e;

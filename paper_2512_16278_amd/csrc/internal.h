@@ -104,12 +104,20 @@ hipError_t launch_eig_lane_batch(int cls, const EigArgs* items, const int64_t* c
                                  int64_t total, hipStream_t s, int wg = 256, bool tri = false);
 hipError_t launch_eig_wave_batch(int precision, int max_nbeam, const EigArgs* items,
                                  const int64_t* cell0, int nitem, int64_t total, hipStream_t s);
-// The per-wave tridiagonal solver: template class of a beam count (local
-// block size of its 8 x 8 lane grid; 0 = none) and its batched launch over
-// items of one class.
+// The tridiagonal solver: class of a beam count (the largest one its kernel
+// instance holds; 0 = none) and its batched launch over items of one class.
+// Up to 40 beams eig_row.hip runs four cells per wave, above eig_tri.hip one.
+// cell0 of a batched launch: every item's range of cells is padded to a
+// multiple of kTriCellPad.
+constexpr int kTriCellPad = 16;
 int eig_tri_class(int n);
 hipError_t launch_eig_tri_batch(int cls, const EigArgs* items, const int64_t* cell0, int nitem,
-                                int64_t total, hipStream_t s, bool v1 = false);
+                                int64_t total, hipStream_t s);
+int eig_row_class(int n);
+// wide: int64 cell records; nc: the non-centred matrix with baseline zb
+hipError_t launch_eig_row(int cls, const EigArgs& a, const EigArgs* items, const int64_t* cell0,
+                          int nitem, int64_t total, bool wide, const double* zb, bool nc,
+                          hipStream_t s);
 
 // ArPLS bandpass of every (beam, sub-interval) from the channel sums (rows
 // layout sum_x[b][cell]); z [nbeam][ncell] FP64; passes [nsub][nbeam] or NULL;

@@ -291,7 +291,7 @@ __global__ __launch_bounds__(kRowThreads, (S == 1 ? 3 : 2)) void eig_row_kernel(
         double pv = pe * xe;
         static_for<a0, S>([&](auto A_) { pv = fma(p[RFI_CI(A_)], x[RFI_CI(A_)], pv); });
         pv = group_sum<16>(pv);
-        const double kk = 0.5 * gm * gm * pv;
+        const double kk = 0.5 * gm * (gm * pv);   // (gm^2 may overflow)
         double w[S], we = 0.0;
         static_for<0, S>([&](auto A_) {
           constexpr int a = RFI_CI(A_);
@@ -331,7 +331,7 @@ __global__ __launch_bounds__(kRowThreads, (S == 1 ? 3 : 2)) void eig_row_kernel(
     constexpr int Q = (N + 15) / 16;
     double* const z = T + 5 * N;
     double ev[Q];
-    all_eigenvalues<16, Q>(ae, n, l, sp, kFloor, (int*)z, ev);
+    all_eigenvalues<16, Q>(ae, n, l, sp, kFloor, z, ev);
 #pragma unroll
     for (int s = 0; s < Q; ++s)
       if (l + 16 * s < n) z[l + 16 * s] = ev[s];

@@ -310,7 +310,7 @@ __global__ __launch_bounds__(64, N <= 48 ? 3 : 2) void eig_tri_kernel(
       double pv = pe * xe;
       static_for<g0, NV>([&](auto G_) { pv = fma(P[RFI_CI(G_)], V[RFI_CI(G_)], pv); });
       pv = group_sum<16>(pv);
-      const double kk = 0.5 * gm * gm * pv;
+      const double kk = 0.5 * gm * (gm * pv);   // (gm^2 may overflow)
       // w vanishes at the rows already reduced, so their columns stay
       const double w = E + l > k ? fma(-kk, x, gm * p) : 0.0;
       const double we = fma(-kk, xe, gm * pe);
@@ -342,7 +342,7 @@ __global__ __launch_bounds__(64, N <= 48 ? 3 : 2) void eig_tri_kernel(
     constexpr int Q = (N + 63) / 64;
     double* const z = lds + 5 * N;
     double ev[Q];
-    all_eigenvalues<64, Q>(ae, n, l, sp, kFloor, (int*)z, ev);
+    all_eigenvalues<64, Q>(ae, n, l, sp, kFloor, z, ev);
 #pragma unroll
     for (int s = 0; s < Q; ++s)
       if (l + 64 * s < n) z[l + 64 * s] = ev[s];

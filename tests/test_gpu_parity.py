@@ -109,6 +109,30 @@ def test_ccm_shapes_bit_exact(dev, nbeam, nchan, L):
         assert np.array_equal(sxy, rsxy), (nbeam, nchan, L, v)
 
 
+@pytest.mark.parametrize("nbeam,nchan,L", [
+    (2, 40, 255), (2, 40, 257), (7, 65, 2047), (15, 16, 4099), (19, 130, 1056), (19, 64, 20345),
+    (31, 20, 800), (36, 33, 2080), (47, 40, 1057), (63, 17, 1500), (72, 20, 1500), (79, 16, 1111)])
+def test_ccm_time_parts(dev, nbeam, nchan, L):
+    """Few tiles of long sub-intervals: several workgroups share a tile's samples (ragged last
+    part, last chunk and channel tile), bit-exact; then accumulated on top of themselves."""
+    import torch
+    from paper_2512_16278_amd import rfi
+    rng = np.random.default_rng(nbeam * 7 + nchan + L)
+    nsub = 2
+    x = rng.integers(0, 256, size=(nbeam, nsub * L + 3, nchan), dtype=np.uint8)
+    S, S2 = ccm.sums_fp64(x, L, nsub, t0=1)
+    rsx, rsxy = packed_oracle_sums(S, S2)
+    say("ccm parts", nbeam, nchan, L)
+    sx, sxy, cnt, (buf, blk, dsx, dsxy, dcnt) = run_ccm(x, L, nsub, dev, 1, t0=1)
+    assert np.array_equal(sx, rsx) and np.array_equal(sxy, rsxy) and (cnt == L).all()
+    if 2 * L <= 33025:
+        rfi.rfi_ccm_accumulate(blk, 1, L, nsub, dsx, dsxy, dcnt, accumulate=1, variant=1)
+        torch.cuda.synchronize()
+        assert np.array_equal(dsx.cpu().numpy(), 2 * rsx)
+        assert np.array_equal(dsxy.cpu().numpy(), 2 * rsxy)
+        assert (dcnt.cpu().numpy() == 2 * L).all()
+
+
 def test_ccm_accumulate_across_calls(dev):
     import torch
     from paper_2512_16278_amd import rfi
@@ -246,6 +270,57 @@ def test_eig_tridiag(dev, nbeam):
     out = _eig_case(dev, x, L, nsub, 32, 3)
     status, _ = _check_eig(x, L, nsub, out, 1e-6, 1e-12)
     assert (status == 0).all()
+
+
+@pytest.mark.parametrize("nbeam", [15, 16, 17, 20, 21, 24, 25, 32, 33, 37, 40, 41, 48, 49, 63, 66,
+                                   73])
+def test_eig_tridiag_instances(dev, nbeam):
+    """The ends of every kernel instance's beam counts and a cell count that is no multiple of a
+    workgroup's 16: as test_eig_tridiag, and the whole-block call (cell records) with eigenvalues
+    and vectors equal to the separate calls (rows layout) bit for bit."""
+    import torch
+    from paper_2512_16278_amd import rfi
+    rng = np.random.default_rng(900 + nbeam)
+    L, nsub, nc = 160, 3, 11
+    x = np.clip(np.rint(128 + 20 * rng.standard_normal((nbeam, nsub * L, nc))), 0, 255).astype(np.uint8)
+    common = np.rint(12 * np.sin(np.arange(nsub * L) / 3.0)).astype(np.int64)
+    x[:, :, 2] = np.clip(x[:, :, 2].astype(np.int64) + common[None, :], 0, 255)
+    x[: nbeam // 2, :, 5] = np.clip(x[: nbeam // 2, :, 5].astype(np.int64) + common[None, :], 0, 255)
+    out = _eig_case(dev, x, L, nsub, 32, 3)
+    status, _ = _check_eig(x, L, nsub, out, 1e-6, 1e-12)
+    assert (status == 0).all()
+    if nbeam <= 20:
+        return                              # the whole-block call takes the per-lane solver
+    blk = rfi.make_block(upload(x, dev), nc)
+    p = rfi.process_params(L, nsub)
+    ws = torch.empty(rfi.rfi_process_workspace_size(nbeam, nc, p), dtype=torch.uint8, device=dev)
+    stat, st8, ev, v1 = eig_buffers(nbeam, nsub * nc, dev)
+    mask = torch.empty(nsub * nc, dtype=torch.uint8, device=dev)
+    rfi.rfi_process_block(blk, p, stat, st8, mask, ws, eigvals=ev, v1=v1)
+    torch.cuda.synchronize()
+    for a, b in zip(out, (stat, st8, ev, v1)):
+        assert np.array_equal(a, b.cpu().numpy())
+
+
+@pytest.mark.parametrize("nbeam", [6, 19, 36, 45, 70])
+def test_eig_tridiag_decoupled(dev, nbeam):
+    """Correlation matrices that fall apart: identical beams (one large eigenvalue, zeros), dead
+    beams (exact ones, off-diagonal zeros) and all beams alike but for one. Eigenvalues within
+    1e-6 of lambda_1, statistic within 1e-12 of the oracle's."""
+    rng = np.random.default_rng(60 + nbeam)
+    L, nc = 128, 6
+    x = np.clip(np.rint(128 + 20 * rng.standard_normal((nbeam, L, nc))), 0, 255).astype(np.uint8)
+    x[:, :, 0] = x[0, :, 0]                     # all alike
+    x[1:, :, 1] = x[1, :, 1]                    # all alike but beam 0
+    x[nbeam // 2:, :, 2] = 77                   # half of them dead
+    x[1:, :, 3] = 5                             # one alive
+    x[:, :, 4] = 9                              # none
+    stat, status, ev, _ = _eig_case(dev, x, L, 1, 32, 3)
+    cr = pipeline.cells(x, L, 1)
+    w = cr.w.reshape(nc, nbeam)
+    assert np.abs(ev.T - w).max() <= 1e-6 * nbeam
+    assert np.abs(stat - cr.stat.ravel()).max() <= 1e-12
+    assert (status == np.where(cr.degenerate.ravel(), 1, 0)).all()
 
 
 def test_eig_tridiag_72_beams_many_cells(dev):

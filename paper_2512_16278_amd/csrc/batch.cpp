@@ -223,6 +223,14 @@ void fill_descriptors(const rfi_batch_item* items, BatchPlan* bpn, char* ws) {
   int pos = 0;
   for (auto& cls : bpn->ccm_classes) {
     int wg = 0;
+    // chunks (and an epilogue of about 8) per workgroup slot of the class
+    int64_t share = 0;
+    for (int k : cls.items) {
+      const ItemPlan& ip = bpn->plans[k];
+      const rfi_batch_item& it = items[ip.idx];
+      share += (int64_t)it.nsub * ((ip.nchan + ip.cc.cw - 1) / ip.cc.cw) * (ccm_chunks(it.L) + 8);
+    }
+    share /= bpn->plans[cls.items[0]].cc.slots;
     for (int k : cls.items) {
       const ItemPlan& ip = bpn->plans[k];
       const rfi_batch_item& it = items[ip.idx];
@@ -239,7 +247,8 @@ void fill_descriptors(const rfi_batch_item* items, BatchPlan* bpn, char* ws) {
       c.nh = ip.cc.nh;
       c.wg0 = wg;
       c.layout = ip.solver == RFI_EIG_TRIDIAG ? 1 : 0;
-      wg += (c.nsub * c.nct + 7) / 8 * 8;
+      c.parts = ccm_item_parts(it.L, share);
+      wg += (c.nsub * c.nct * c.parts + 7) / 8 * 8;
     }
   }
   // eigen descriptors, class by class, with the first global cell of each
@@ -290,8 +299,10 @@ hipError_t enqueue_ccm(const BatchPlan& bpn, const void* desc, char* ws, hipStre
   for (const CcmLaunchClass& cls : bpn.ccm_classes) {
     const int m = (int)cls.items.size();
     const CcmItem& last = hci[pos + m - 1];
-    const int total = last.wg0 + (last.nsub * last.nct + 7) / 8 * 8;
-    hipError_t e = launch_ccm_batch(cls.nbeam, &cls.ct, ci + pos, m, total, s);
+    const int total = last.wg0 + (last.nsub * last.nct * last.parts + 7) / 8 * 8;
+    bool parts = false;
+    for (int i = 0; i < m; ++i) parts |= hci[pos + i].parts > 1;
+    hipError_t e = launch_ccm_batch(cls.nbeam, &cls.ct, ci + pos, m, total, parts, s);
     if (e != hipSuccess) return e;
     pos += m;
   }

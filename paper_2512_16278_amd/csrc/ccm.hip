@@ -95,6 +95,7 @@ struct MfmaCfg {
                                  ? (NEED + 1023) / 1024 * 1024
                                  : LDS_MAX;
   static constexpr int STG_BYTES = LDS - STG_OFF;
+  static constexpr int SLOTS = 256 * (LDS_MAX / LDS < 2 ? 1 : 2);  // workgroups the chip holds
   static constexpr bool FITS = RING <= LDS_MAX && STG_BYTES >= STG_MIN;
 };
 
@@ -138,7 +139,7 @@ __global__ __launch_bounds__((MfmaCfg<NB, CW, CPW, IPW, NST>::NTHR), 1) void ccm
     BeamPtrs bp, int nbeam, int nchan, int64_t row_stride, int64_t t0, int L, int nsub,
     int nct, int32_t* __restrict__ sum_x, int32_t* __restrict__ sum_xy,
     int32_t* __restrict__ count, int accumulate, int G, int nh, int prio, int layout,
-    int64_t kstride, int ksplit, const CcmItem* __restrict__ items, int nitem) {
+    int64_t kstride, int ksplit, int parts, const CcmItem* __restrict__ items, int nitem) {
   using C = MfmaCfg<NB, CW, CPW, IPW, NST>;
   // the beam pointer table is the first kernel argument: index it in place
   const uint8_t* const* beam_tab = (const uint8_t* const*)__builtin_amdgcn_kernarg_segment_ptr();
@@ -165,8 +166,9 @@ __global__ __launch_bounds__((MfmaCfg<NB, CW, CPW, IPW, NST>::NTHR), 1) void ccm
     sum_xy = it.sum_xy;
     count = it.count;
     layout = it.layout;
+    parts = it.parts;
     w -= it.wg0;
-    if (w >= nsub * nct) return;      // padding to a multiple of 8 workgroups
+    if (w >= nsub * nct * parts) return;      // padding to a multiple of 8 workgroups
     kstride = 0;
     ksplit = 1;
   }
@@ -185,8 +187,7 @@ __global__ __launch_bounds__((MfmaCfg<NB, CW, CPW, IPW, NST>::NTHR), 1) void ccm
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = tid >> 6;
-  const int ntiles = nsub * nct;
-  const int nchunk = (L + TC - 1) / TC;
+  const int ntiles = nsub * nct * parts;
   const int64_t ncell = (int64_t)nsub * nchan;
   const int nrow = nbeam + nbeam * (nbeam + 1) / 2;
 
@@ -201,6 +202,15 @@ __global__ __launch_bounds__((MfmaCfg<NB, CW, CPW, IPW, NST>::NTHR), 1) void ccm
     const int u = w / (8 * G), rem = w % (8 * G);
     tile = G * (8 * u + rem % 8) + rem / 8;
   }
+  // tile = (sub-interval k, part, channel tile): with parts > 1 the samples of
+  // k are shared out in whole chunks, this workgroup takes [r0, r0 + Lp) and
+  // adds its sums to the outputs (zero before the launch, or the caller's)
+  const int k = tile / nct / parts, part = tile / nct % parts;
+  const int per = ((L + TC - 1) / TC + parts - 1) / parts * TC;
+  const int r0 = part * per;
+  const int Lp = L - r0 < per ? L - r0 : per;
+  if (Lp <= 0) return;                        // more parts than this needs
+  const int nchunk = (Lp + TC - 1) / TC;
 
   // Per chunk this thread's lane fills unit (64 q + lane) of the buffer for
   // q = wave + NWAVE i, i < IPW; decode which (beam, row, seg) lands there.
@@ -222,11 +232,10 @@ __global__ __launch_bounds__((MfmaCfg<NB, CW, CPW, IPW, NST>::NTHR), 1) void ccm
   }
   // DMA of chunk `chunk` of tile T into ring buffer `slot`
   auto issue = [&](int T, int chunk, int slot) {
-    const int k = T / nct;
     const int c0 = (T % nct) * CW;
     uint8_t* buf = lds + slot * C::STAGE;
-    const int rows = min(TC, L - chunk * TC);
-    const int64_t row = t0 + (int64_t)(k / ksplit) * kstride + (int64_t)(k % ksplit) * L +
+    const int rows = min(TC, Lp - chunk * TC);
+    const int64_t row = t0 + (int64_t)(k / ksplit) * kstride + (int64_t)(k % ksplit) * L + r0 +
                         (int64_t)chunk * TC;
 #pragma unroll
     for (int i = 0; i < IPW; ++i) {
@@ -339,7 +348,6 @@ __global__ __launch_bounds__((MfmaCfg<NB, CW, CPW, IPW, NST>::NTHR), 1) void ccm
   const int cwp = CW / nh;
   const int ch_st = tid % cwp, row_st = tid / cwp, rstep = C::NTHR / cwp;
   auto epilogue = [&](int T) {
-    const int k = T / nct;
     const int c0 = (T % nct) * CW;
     for (int r = tid; r < nrow; r += C::NTHR) {
       int a = r, b = 255;
@@ -368,7 +376,7 @@ __global__ __launch_bounds__((MfmaCfg<NB, CW, CPW, IPW, NST>::NTHR), 1) void ccm
             }
           }
     }
-    const uint32_t cnt = (uint32_t)L;
+    const uint32_t cnt = (uint32_t)Lp;
     const int mypass = cb / cwp;
     for (int h = 0; h < nh; ++h) {
       if (mypass == h) {
@@ -414,12 +422,13 @@ __global__ __launch_bounds__((MfmaCfg<NB, CW, CPW, IPW, NST>::NTHR), 1) void ccm
           int32_t* dst = layout ? rec + row
                                 : (row < nbeam ? sum_x + (int64_t)row * ncell
                                                : sum_xy + (int64_t)(row - nbeam) * ncell) + cell;
-          *dst = accumulate ? (int32_t)((uint32_t)*dst + raw) : (int32_t)raw;
+          if (parts > 1) atomicAdd((unsigned*)dst, raw);   // integers: exact in any order
+          else *dst = accumulate ? (int32_t)((uint32_t)*dst + raw) : (int32_t)raw;
         }
       }
       lds_barrier();
     }
-    if (c0 == 0 && tid == 0) count[k] = accumulate ? count[k] + L : L;
+    if (c0 == 0 && part == 0 && tid == 0) count[k] = accumulate ? count[k] + L : L;
   };
 
   // ring of NST buffers: chunks c+1 .. c+NST-2 (and c+NST-1 once issued) are
@@ -430,10 +439,10 @@ __global__ __launch_bounds__((MfmaCfg<NB, CW, CPW, IPW, NST>::NTHR), 1) void ccm
     const int slot = c % NST;
     wait_chunk<IPW, NST>(last_issued - c);          // chunk c complete in LDS
     if (c + NST - 1 < nchunk) issue(tile, c + NST - 1, (c + NST - 1) % NST);  // buffer of c - 1
-    if (c == nchunk - 1 && L % TC != 0) {
-      // short last chunk: its rows past L hold dummy data; overwrite them
-      // with 0x80 bytes (0 after the offset XOR)
-      const int rows = L - c * TC;
+    if (c == nchunk - 1 && Lp % TC != 0) {
+      // short last chunk: its rows past the range hold dummy data; overwrite
+      // them with 0x80 bytes (0 after the offset XOR)
+      const int rows = Lp - c * TC;
       uint8_t* buf = lds + slot * C::STAGE;
       const int nu = nbeam * (TC - rows) * C::SEGS;
       for (int u = tid; u < nu; u += C::NTHR) {
@@ -463,6 +472,51 @@ int epilogue_passes(int nbeam) {
   return nrow * (CW / nh + 1) * 4 > C::STG_BYTES ? 0 : nh;
 }
 
+// Zeroes two int32 arrays (the outputs of a launch in parts).
+__global__ __launch_bounds__(256) void zero_kernel(int32_t* a, int64_t na, int32_t* b, int64_t nb) {
+  const int64_t step = (int64_t)gridDim.x * 256;
+  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < na + nb; i += step)
+    *(i < na ? a + i : b + (i - na)) = 0;
+}
+hipError_t launch_zero(int32_t* a, int64_t na, int32_t* b, int64_t nb, hipStream_t s) {
+  const int64_t blocks = (na + nb + 2047) / 2048;
+  hipLaunchKernelGGL(zero_kernel, dim3((unsigned)(blocks < 2048 ? blocks : 2048)), dim3(256), 0, s,
+                     a, na, b, nb);
+  return hipGetLastError();
+}
+// the outputs of the batched items in parts
+__global__ __launch_bounds__(256) void zero_items_kernel(const CcmItem* items) {
+  const CcmItem& it = items[blockIdx.y];
+  if (it.parts == 1) return;
+  const int64_t ncell = (int64_t)it.nsub * it.nchan, np = (int64_t)it.nbeam * (it.nbeam + 1) / 2;
+  const int64_t na = ncell * (it.layout ? it.nbeam + np : it.nbeam), nb = it.layout ? 0 : ncell * np;
+  const int64_t step = (int64_t)gridDim.x * 256;
+  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < na + nb; i += step)
+    *(i < na ? it.sum_x + i : it.sum_xy + (i - na)) = 0;
+}
+
+// Workgroups per tile of a launch of ntiles tiles on `slots` workgroup slots:
+// a launch that leaves CUs idle, or whose last round is nearly empty, shares
+// the samples of a tile out. Cost in chunks per slot: rounds x (chunks +
+// epilogue, with a zeroing launch and atomic stores in place of plain ones
+// when shared); shared only for a gain of a tenth. 19 beams: 16 tiles of 1024
+// samples in 8 parts 49 -> 20 us (and 3 us to zero); 640 tiles of 20345 samples
+// in 2 parts, 3 rounds -> 5 half ones, 3.30 -> 2.95 ms.
+int ccm_parts(int64_t ntiles, int L, int slots) {
+  const int nchunk = (L + TC - 1) / TC;
+  if (ntiles >= 4 * slots || nchunk < 8) return 1;
+  int64_t best = (ntiles + slots - 1) / slots * (nchunk + 8) * 9 / 10;
+  int parts = 1;
+  for (int p = 2; p <= 32 && p * 4 <= nchunk; ++p) {
+    const int64_t cost = (ntiles * p + slots - 1) / slots * ((nchunk + p - 1) / p + 12) + 4;
+    if (cost < best) {
+      best = cost;
+      parts = p;
+    }
+  }
+  return parts;
+}
+
 template <int NB, int CW, int CPW, int IPW, int NST>
 hipError_t launch_mfma_cfg(const BeamPtrs& bp, int nbeam, int nchan, int64_t row_stride,
                            int64_t t0, int L, int nsub, int32_t* sum_x, int32_t* sum_xy,
@@ -481,9 +535,16 @@ hipError_t launch_mfma_cfg(const BeamPtrs& bp, int nbeam, int nchan, int64_t row
   const int64_t ntiles = (int64_t)nsub * nct;
   const int G = group_tiles(CW, group_bytes);
   const int prio = 0;   // raised issue priority of the streaming waves measured no gain
-  hipLaunchKernelGGL(kern, dim3((unsigned)ntiles), dim3(C::NTHR), C::LDS, s, bp, nbeam, nchan,
+  const int parts = ccm_parts(ntiles, L, C::SLOTS);
+  if (parts > 1 && !accumulate) {
+    const int64_t ncell = (int64_t)nsub * nchan;
+    const int64_t nx = layout ? ncell * (nbeam + npair_of(nbeam)) : ncell * nbeam;
+    e = launch_zero(sum_x, nx, layout ? nullptr : sum_xy, layout ? 0 : ncell * npair_of(nbeam), s);
+    if (e != hipSuccess) return e;
+  }
+  hipLaunchKernelGGL(kern, dim3((unsigned)(ntiles * parts)), dim3(C::NTHR), C::LDS, s, bp, nbeam, nchan,
                      row_stride, t0, L, nsub, nct, sum_x, sum_xy, count, accumulate, G, nh, prio,
-                     layout, kstride, ksplit, (const CcmItem*)nullptr, 0);
+                     layout, kstride, ksplit, parts, (const CcmItem*)nullptr, 0);
   return hipGetLastError();
 }
 
@@ -500,7 +561,7 @@ hipError_t launch_batch_cfg(const CcmItem* items, int nitem, int total_wg, int g
   memset(&none, 0, sizeof(none));
   hipLaunchKernelGGL(kern, dim3((unsigned)total_wg), dim3(C::NTHR), C::LDS, s, none, 0, 0,
                      (int64_t)0, (int64_t)0, 0, 0, 0, (int32_t*)nullptr, (int32_t*)nullptr,
-                     (int32_t*)nullptr, 0, G, 1, 0, 0, (int64_t)0, 1, items, nitem);
+                     (int32_t*)nullptr, 0, G, 1, 0, 0, (int64_t)0, 1, 1, items, nitem);
   return hipGetLastError();
 }
 
@@ -591,6 +652,7 @@ struct Describe {
     out->key = ((NB * 128 + CW) * 16 + CPW) * 16 * 8 + IPW * 8 + NST;
     out->cw = CW;
     out->nh = epilogue_passes<NB, CW, CPW, IPW, NST>(nbeam);
+    out->slots = MfmaCfg<NB, CW, CPW, IPW, NST>::SLOTS;
     return out->nh > 0 ? hipSuccess : hipErrorInvalidValue;
   }
 };
@@ -693,8 +755,22 @@ hipError_t ccm_class(int nbeam, CcmClass* c, const CcmTune* t) {
   return e;
 }
 
+int ccm_item_parts(int L, int64_t share) {
+  // a workgroup takes at most half a slot's share of the launch, so that the
+  // items of long sub-intervals do not outlast the others
+  const int nchunk = (L + TC - 1) / TC;
+  const int64_t most = share / 2 > 8 ? share / 2 : 8;
+  if (nchunk <= most) return 1;
+  const int64_t p = (nchunk + most - 1) / most;
+  return (int)(p < 32 ? p : 32);
+}
+
+int ccm_chunks(int L) { return (L + TC - 1) / TC; }
+
 hipError_t launch_ccm_batch(int nbeam_of_class, const CcmTune* t, const CcmItem* items,
-                            int nitem, int total_wg, hipStream_t s) {
+                            int nitem, int total_wg, bool parts, hipStream_t s) {
+  if (parts)
+    hipLaunchKernelGGL(zero_items_kernel, dim3(256, (unsigned)nitem), dim3(256), 0, s, items);
   LaunchBatch op{items, nitem, total_wg, t ? t->group_bytes : 0, s};
   return ccm_dispatch(nbeam_of_class, 0, op, t);
 }

@@ -16,7 +16,8 @@ struct BeamPtrs {
 inline int npair_of(int n) { return n * (n + 1) / 2; }
 
 // One block of a batched sums launch (device descriptor). The block's
-// workgroups are [wg0, wg0 + 8 ceil(nsub * nct / 8)); wg0 is a multiple of 8.
+// workgroups are [wg0, wg0 + 8 ceil(nsub * nct * parts / 8)); wg0 is a multiple
+// of 8.
 struct CcmItem {
   const uint8_t* const* beams;   // device table [nbeam] of beam pointers
   int64_t row_stride, t0;
@@ -25,6 +26,7 @@ struct CcmItem {
   int32_t* count;
   int32_t nbeam, nchan, L, nsub;
   int32_t nct, nh, wg0, layout;  // layout: as the sums engine's argument
+  int32_t parts, pad;            // workgroups per tile (ccm_item_parts)
 };
 // Launch choices of the MFMA sums engine (all 0 = defaults): tile = variant
 // index of the beam count's tile shapes (< ccm_tile_variants), stages = cap
@@ -38,13 +40,18 @@ int ccm_tile_variants(int nbeam);
 // class share a batched launch; cw = channels per tile, nh = epilogue passes.
 struct CcmClass {
   long long key;
-  int cw, nh, group_bytes;
+  int cw, nh, group_bytes, slots;   // slots: workgroups of the class the chip holds
 };
 hipError_t ccm_class(int nbeam, CcmClass* c, const CcmTune* t = nullptr);
 // Batched sums launch over the items of one class (items in device memory,
-// sorted by wg0); nbeam_of_class is any member's beam count, t its choices.
+// sorted by wg0); nbeam_of_class is any member's beam count, t its choices;
+// parts: some item has more than one workgroup per tile.
 hipError_t launch_ccm_batch(int nbeam_of_class, const CcmTune* t, const CcmItem* items,
-                            int nitem, int total_wg, hipStream_t s);
+                            int nitem, int total_wg, bool parts, hipStream_t s);
+// Workgroups per tile of an item of sub-intervals of L samples when a slot's
+// share of the whole launch is `share` chunks; chunks of L samples.
+int ccm_item_parts(int L, int64_t share);
+int ccm_chunks(int L);
 
 // Kernel launchers (return a HIP error code; arguments already validated).
 // kstride: samples from the start of one sub-interval to the next (0 = L:

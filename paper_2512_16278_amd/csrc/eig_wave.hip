@@ -119,6 +119,15 @@ __global__ __launch_bounds__(64) void eig_wave_kernel(EigArgs g, const EigArgs* 
   __syncthreads();
 
   const T eps = Eps<T>::v;
+  const int i0 = lane / h, k0 = lane % h, di = 64 / h, dk = 64 % h;
+  auto step = [&](int& i, int& k) {
+    i += di;
+    k += dk;
+    if (k >= h) {
+      k -= h;
+      ++i;
+    }
+  };
   int sweep = 0, last = 0;
   for (; sweep < g.max_sweeps; ++sweep) {
     int rot_sweep = 0;
@@ -151,8 +160,9 @@ __global__ __launch_bounds__(64) void eig_wave_kernel(EigArgs g, const EigArgs* 
       if (!__syncthreads_or(rotated)) continue;
       rot_sweep = 1;
       // A <- A J, V <- V J: column pairs (p, q) of every row i
-      for (int w = lane; w < n * h; w += 64) {
-        const int k = w % h, i = w / h;
+      // (the pair k and row or column i of element w, stepped by 64 without
+      // the division that a wave-uniform but unknown h would cost each time)
+      for (int i = i0, k = k0; i < n; step(i, k)) {
         const T s = Ss[k];
         if (s == (T)0) continue;
         const int p = P[k], q = Q[k];
@@ -166,8 +176,7 @@ __global__ __launch_bounds__(64) void eig_wave_kernel(EigArgs g, const EigArgs* 
       }
       __syncthreads();
       // A <- J^T A: row pairs (p, q) of every column j
-      for (int w = lane; w < n * h; w += 64) {
-        const int k = w % h, j = w / h;
+      for (int j = i0, k = k0; j < n; step(j, k)) {
         const T s = Ss[k];
         if (s == (T)0) continue;
         const int p = P[k], q = Q[k];

@@ -139,7 +139,7 @@ __global__ __launch_bounds__((MfmaCfg<NB, CW, CPW, IPW, NST>::NTHR), 1) void ccm
     BeamPtrs bp, int nbeam, int nchan, int64_t row_stride, int64_t t0, int L, int nsub,
     int nct, int32_t* __restrict__ sum_x, int32_t* __restrict__ sum_xy,
     int32_t* __restrict__ count, int accumulate, int G, int nh, int prio, int layout,
-    int64_t kstride, int ksplit, int parts, const CcmItem* __restrict__ items, int nitem) {
+    int64_t kstride, int ksplit, int Llast, int parts, const CcmItem* __restrict__ items, int nitem) {
   using C = MfmaCfg<NB, CW, CPW, IPW, NST>;
   // the beam pointer table is the first kernel argument: index it in place
   const uint8_t* const* beam_tab = (const uint8_t* const*)__builtin_amdgcn_kernarg_segment_ptr();
@@ -171,11 +171,13 @@ __global__ __launch_bounds__((MfmaCfg<NB, CW, CPW, IPW, NST>::NTHR), 1) void ccm
     if (w >= nsub * nct * parts) return;      // padding to a multiple of 8 workgroups
     kstride = 0;
     ksplit = 1;
+    Llast = L;
   }
   // sub-interval k of the launch starts at t0 + (k / ksplit) kstride +
   // (k mod ksplit) L: with ksplit = 1 and kstride = L they are back to back; a
   // longer stride sums one time chunk of each of several long sub-intervals,
-  // and ksplit > 1 cuts each of those into ksplit consecutive chunks of L
+  // and ksplit > 1 cuts each of those into ksplit consecutive chunks of L, the
+  // last one of Llast <= L
   if (kstride == 0) kstride = L;
   // optional issue priority over waves of other kernels on the same SIMD
   if (prio) __builtin_amdgcn_s_setprio(2);
@@ -206,9 +208,10 @@ __global__ __launch_bounds__((MfmaCfg<NB, CW, CPW, IPW, NST>::NTHR), 1) void ccm
   // k are shared out in whole chunks, this workgroup takes [r0, r0 + Lp) and
   // adds its sums to the outputs (zero before the launch, or the caller's)
   const int k = tile / nct / parts, part = tile / nct % parts;
-  const int per = ((L + TC - 1) / TC + parts - 1) / parts * TC;
+  const int Lk = k % ksplit == ksplit - 1 ? Llast : L;
+  const int per = ((Lk + TC - 1) / TC + parts - 1) / parts * TC;
   const int r0 = part * per;
-  const int Lp = L - r0 < per ? L - r0 : per;
+  const int Lp = Lk - r0 < per ? Lk - r0 : per;
   if (Lp <= 0) return;                        // more parts than this needs
   const int nchunk = (Lp + TC - 1) / TC;
 
@@ -428,7 +431,7 @@ __global__ __launch_bounds__((MfmaCfg<NB, CW, CPW, IPW, NST>::NTHR), 1) void ccm
       }
       lds_barrier();
     }
-    if (c0 == 0 && part == 0 && tid == 0) count[k] = accumulate ? count[k] + L : L;
+    if (c0 == 0 && part == 0 && tid == 0) count[k] = accumulate ? count[k] + Lk : Lk;
   };
 
   // ring of NST buffers: chunks c+1 .. c+NST-2 (and c+NST-1 once issued) are
@@ -521,7 +524,7 @@ template <int NB, int CW, int CPW, int IPW, int NST>
 hipError_t launch_mfma_cfg(const BeamPtrs& bp, int nbeam, int nchan, int64_t row_stride,
                            int64_t t0, int L, int nsub, int32_t* sum_x, int32_t* sum_xy,
                            int32_t* count, int accumulate, int group_bytes, int layout,
-                           int64_t kstride, int ksplit, hipStream_t s) {
+                           int64_t kstride, int ksplit, int Llast, hipStream_t s) {
   using C = MfmaCfg<NB, CW, CPW, IPW, NST>;
   if ((int64_t)nbeam * C::UPB > (int64_t)64 * IPW * C::NWAVE) return hipErrorInvalidValue;
   if (nbeam > C::MAXB) return hipErrorInvalidValue;
@@ -535,7 +538,7 @@ hipError_t launch_mfma_cfg(const BeamPtrs& bp, int nbeam, int nchan, int64_t row
   const int64_t ntiles = (int64_t)nsub * nct;
   const int G = group_tiles(CW, group_bytes);
   const int prio = 0;   // raised issue priority of the streaming waves measured no gain
-  const int parts = ccm_parts(ntiles, L, C::SLOTS);
+  const int parts = ksplit > 1 ? 1 : ccm_parts(ntiles, L, C::SLOTS);   // (already cut)
   if (parts > 1 && !accumulate) {
     const int64_t ncell = (int64_t)nsub * nchan;
     const int64_t nx = layout ? ncell * (nbeam + npair_of(nbeam)) : ncell * nbeam;
@@ -544,7 +547,7 @@ hipError_t launch_mfma_cfg(const BeamPtrs& bp, int nbeam, int nchan, int64_t row
   }
   hipLaunchKernelGGL(kern, dim3((unsigned)(ntiles * parts)), dim3(C::NTHR), C::LDS, s, bp, nbeam, nchan,
                      row_stride, t0, L, nsub, nct, sum_x, sum_xy, count, accumulate, G, nh, prio,
-                     layout, kstride, ksplit, parts, (const CcmItem*)nullptr, 0);
+                     layout, kstride, ksplit, Llast, parts, (const CcmItem*)nullptr, 0);
   return hipGetLastError();
 }
 
@@ -561,7 +564,7 @@ hipError_t launch_batch_cfg(const CcmItem* items, int nitem, int total_wg, int g
   memset(&none, 0, sizeof(none));
   hipLaunchKernelGGL(kern, dim3((unsigned)total_wg), dim3(C::NTHR), C::LDS, s, none, 0, 0,
                      (int64_t)0, (int64_t)0, 0, 0, 0, (int32_t*)nullptr, (int32_t*)nullptr,
-                     (int32_t*)nullptr, 0, G, 1, 0, 0, (int64_t)0, 1, 1, items, nitem);
+                     (int32_t*)nullptr, 0, G, 1, 0, 0, (int64_t)0, 1, 0, 1, items, nitem);
   return hipGetLastError();
 }
 
@@ -634,13 +637,13 @@ struct LaunchOne {
   int32_t *sum_x, *sum_xy, *count;
   int accumulate, group_bytes, layout;
   int64_t kstride;
-  int ksplit;
+  int ksplit, Llast;
   hipStream_t s;
   template <int NB, int CW, int CPW, int IPW, int NST>
   hipError_t run() {
     return launch_mfma_cfg<NB, CW, CPW, IPW, NST>(bp, nbeam, nchan, row_stride, t0, L, nsub, sum_x,
                                                   sum_xy, count, accumulate, group_bytes, layout,
-                                                  kstride, ksplit, s);
+                                                  kstride, ksplit, Llast, s);
   }
 };
 
@@ -740,10 +743,18 @@ int ccm_tile_variants(int nbeam) {
 hipError_t launch_ccm_mfma(const BeamPtrs& bp, int nbeam, int nchan, int64_t row_stride,
                            int64_t t0, int L, int nsub, int32_t* sum_x, int32_t* sum_xy,
                            int32_t* count, int accumulate, int shared_cu, hipStream_t s,
-                           const CcmTune* t, int layout, int64_t kstride, int ksplit) {
+                           const CcmTune* t, int layout, int64_t kstride, int ksplit, int Llast) {
   LaunchOne op{bp, nbeam, nchan, row_stride, t0, L, nsub, sum_x, sum_xy, count, accumulate,
-               t ? t->group_bytes : 0, layout, kstride, ksplit < 1 ? 1 : ksplit, s};
+               t ? t->group_bytes : 0, layout, kstride, ksplit, Llast, s};
   return ccm_dispatch(nbeam, shared_cu, op, t);
+}
+
+hipError_t launch_ccm_mfma(const BeamPtrs& bp, int nbeam, int nchan, int64_t row_stride,
+                           int64_t t0, int L, int nsub, int32_t* sum_x, int32_t* sum_xy,
+                           int32_t* count, int accumulate, int shared_cu, hipStream_t s,
+                           const CcmTune* t, int layout, int64_t kstride, int ksplit) {
+  return launch_ccm_mfma(bp, nbeam, nchan, row_stride, t0, L, nsub, sum_x, sum_xy, count,
+                         accumulate, shared_cu, s, t, layout, kstride, ksplit, L);
 }
 
 hipError_t ccm_class(int nbeam, CcmClass* c, const CcmTune* t) {

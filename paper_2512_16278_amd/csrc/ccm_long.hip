@@ -1,20 +1,18 @@
 // Sums of Eq. 1 (Sec. 3.2) for sub-intervals longer than the int32 bound
 // (Table 1 runs sub-intervals up to 10 s = 203,450 samples of 49.152 us).
 //
-// Each sub-interval's time range is cut into P chunks of c = floor(L / P)
-// samples plus a remainder of L - P c < P samples. One launch of the sums
-// engine forms the exact int32 sums of every (sub-interval, chunk) pair at
-// once, as if each chunk were a sub-interval of its own (ksplit = P), and a
-// second, small launch those of the remainders; a widening pass then adds the
-// P (+ 1) int32 records of each cell into its int64 record
+// Each sub-interval's time range is cut into P chunks of c samples, the last
+// one shorter. One launch of the sums engine forms the exact int32 sums of every
+// (sub-interval, chunk) pair, as if each chunk were a sub-interval of its own
+// (ksplit = P), and a widening pass adds the P int32 records of each cell into
+// its int64 record
 //     rec[cell][b]          = sum_t x_b(t)
 //     rec[cell][n + pair]   = sum_t x_a(t) x_b(t)
 // exact for any L <= RFI_MAX_COUNT_LONG (|sums| < 255^2 2^18 < 2^34).
 //
-// P is at least ceil(L / RFI_MAX_COUNT) (each chunk within the int32 bound)
-// and large enough that the chunk launch has about 2048 workgroups of 64
-// channels: a single 10 s sub-interval of 4096 channels is only 64 tiles,
-// which as one launch per chunk would leave three quarters of the CUs idle.
+// P is at least ceil(L / RFI_MAX_COUNT) (each chunk within the int32 bound);
+// beyond that it fills the chip's workgroup slots (a single 10 s sub-interval of
+// 4096 channels is only 64 tiles) in whole rounds: see split_for.
 #include <hip/hip_runtime.h>
 
 #include "internal.h"
@@ -28,17 +26,8 @@ constexpr int64_t kTargetTileChannels = (int64_t)2048 * 64;
 
 inline size_t up256(size_t x) { return (x + 255) / 256 * 256; }
 
-// chunks per sub-interval for n sub-intervals of F channels (at most
-// kMaxSplit beyond what exactness needs)
-int split_for(int L, int nsub, int nchan) {
-  const int need = (L + RFI_MAX_COUNT - 1) / RFI_MAX_COUNT;
-  int64_t want = (kTargetTileChannels + (int64_t)nsub * nchan - 1) / ((int64_t)nsub * nchan);
-  if (want > kMaxSplit) want = kMaxSplit;
-  if (want > L / 64) want = L / 64 > 0 ? L / 64 : 1;   // chunks of at least 64 samples
-  return need > (int)want ? need : (int)want;
-}
-
-// largest split any L <= RFI_MAX_COUNT_LONG can take (sizes the scratch)
+// Largest split (sizes the scratch, for any L <= RFI_MAX_COUNT_LONG): about 2048
+// workgroups of 64 channels, at most kMaxSplit beyond what exactness needs.
 int max_split(int nsub, int nchan) {
   const int need = (RFI_MAX_COUNT_LONG + RFI_MAX_COUNT - 1) / RFI_MAX_COUNT;
   int64_t want = (kTargetTileChannels + (int64_t)nsub * nchan - 1) / ((int64_t)nsub * nchan);
@@ -46,13 +35,42 @@ int max_split(int nsub, int nchan) {
   return need > (int)want ? need : (int)want;
 }
 
-// rec64[cell][row] = sum over the P chunk records (and the remainder record
-// when rem) of that cell; count[k] = L. With accumulate the sums and counts
-// are added to what the records and counts hold.
+// Chunks per sub-interval: the least cost, in 32-sample steps of a slot, of
+// rounds x (steps per chunk + a workgroup's prologue and epilogue) and of the
+// records, written by the sums and read by the widening pass (8 bytes a row
+// against the 256 slots x 32 samples x nbeam bytes of a step's channels). The
+// streaming bound is reached by full rounds, not by many workgroups: 19 beams x
+// 4096 channels, 3 sub-intervals of 40690 samples (192 tiles): 11 chunks (2112
+// workgroups, 8.25 rounds) and a launch for the remainder 1971 us with a widening
+// pass of 42 us, 4 chunks (3 rounds) 1826 and 17 us.
+int split_for(int L, int nsub, int nchan, int nbeam, const CcmTune* t) {
+  const int need = (L + RFI_MAX_COUNT - 1) / RFI_MAX_COUNT;
+  CcmClass cc;
+  if (ccm_class(nbeam, &cc, t) != hipSuccess) return need;
+  const int64_t ntiles = (int64_t)nsub * ((nchan + cc.cw - 1) / cc.cw);
+  const int rows = 1 + (nbeam + 1) / 2;       // record rows per beam
+  const int most = max_split(nsub, nchan) < L / 256 ? max_split(nsub, nchan) : L / 256;
+  int best = need;
+  int64_t best_cost = INT64_MAX;
+  for (int p = need; p <= most || p == need; ++p) {
+    const int64_t steps = ((L + p - 1) / p + 31) / 32;
+    const int64_t cost = (ntiles * p + cc.slots - 1) / cc.slots * (steps + 8) +
+                         ntiles * p * rows / 1024;
+    if (cost < best_cost) {
+      best_cost = cost;
+      best = p;
+    }
+  }
+  return best;
+}
+
+// rec64[cell][row] = sum over the P chunk records of that cell; count[k] = L.
+// With accumulate the sums and counts are added to what the records and counts
+// hold.
 __global__ __launch_bounds__(kWidenThreads) void widen_kernel(const int32_t* __restrict__ rec32,
                                                               int64_t* __restrict__ rec64,
                                                               int nsub, int nchan, int nrow,
-                                                              int P, int rem,
+                                                              int P,
                                                               int32_t* __restrict__ count,
                                                               int L, int accumulate) {
   const int64_t per_sub = (int64_t)nchan * nrow;         // values of one sub-interval
@@ -66,7 +84,6 @@ __global__ __launch_bounds__(kWidenThreads) void widen_kernel(const int32_t* __r
   const int32_t* src = rec32 + k * P * per_sub + w;
   int64_t acc = 0;
   for (int j = 0; j < P; ++j) acc += src[(int64_t)j * per_sub];
-  if (rem) acc += rec32[(int64_t)nsub * P * per_sub + i];
   rec64[i] = accumulate ? rec64[i] + acc : acc;
 }
 
@@ -83,8 +100,11 @@ hipError_t launch_ccm_long(const BeamPtrs& bp, int nbeam, int nchan, int64_t row
                            hipStream_t s, const CcmTune* t, int accumulate) {
   if (nsub == 0) return hipSuccess;
   const int nrow = nbeam + npair_of(nbeam);
-  const int P = split_for(L, nsub, nchan);
-  const int c = L / P, rem = L - P * c;
+  const int P = split_for(L, nsub, nchan, nbeam, t);
+  // whole 32-sample steps per chunk where the last one still has samples
+  int c = (L + P - 1) / P;
+  const int c32 = (c + 31) / 32 * 32;
+  if (c32 <= RFI_MAX_COUNT && (int64_t)(P - 1) * c32 < L) c = c32;
   const size_t per_sub = (size_t)nchan * nrow;
   const int Pmax = max_split(nsub, nchan);
   int32_t* rec32 = (int32_t*)tmp;
@@ -92,19 +112,12 @@ hipError_t launch_ccm_long(const BeamPtrs& bp, int nbeam, int nchan, int64_t row
   // every chunk of every sub-interval: launch sub-interval k P + j is chunk j
   // of sub-interval k, records [k P + j][channel][row]
   hipError_t e = launch_ccm_mfma(bp, nbeam, nchan, row_stride, t0, c, nsub * P, rec32, nullptr,
-                                 cnt32, 0, 0, s, t, 1, (int64_t)L, P);
+                                 cnt32, 0, 0, s, t, 1, (int64_t)L, P, L - (P - 1) * c);
   if (e != hipSuccess) return e;
-  if (rem) {
-    // the last rem samples of each sub-interval, records after the chunks'
-    e = launch_ccm_mfma(bp, nbeam, nchan, row_stride, t0 + (int64_t)P * c, rem, nsub,
-                        rec32 + (size_t)nsub * P * per_sub, nullptr, cnt32 + (size_t)nsub * P, 0,
-                        0, s, t, 1, (int64_t)L, 1);
-    if (e != hipSuccess) return e;
-  }
   const int64_t nval = (int64_t)nsub * (int64_t)per_sub;
   const unsigned grid = (unsigned)((nval + kWidenThreads - 1) / kWidenThreads);
   hipLaunchKernelGGL(widen_kernel, dim3(grid), dim3(kWidenThreads), 0, s, rec32, rec, nsub, nchan,
-                     nrow, P, rem, count, L, accumulate);
+                     nrow, P, count, L, accumulate);
   return hipGetLastError();
 }
 

@@ -57,12 +57,18 @@ int ccm_chunks(int L);
 // kstride: samples from the start of one sub-interval to the next (0 = L:
 // back to back; longer strides sum one time chunk of long sub-intervals);
 // ksplit > 1: launch sub-interval k starts at t0 + (k / ksplit) kstride +
-// (k mod ksplit) L (ksplit consecutive chunks of L samples per stride).
+// (k mod ksplit) L (ksplit consecutive chunks of L samples per stride; with
+// Llast the last one of 1 <= Llast <= L samples).
 hipError_t launch_ccm_mfma(const BeamPtrs& bp, int nbeam, int nchan, int64_t row_stride,
                            int64_t t0, int L, int nsub, int32_t* sum_x, int32_t* sum_xy,
                            int32_t* count, int accumulate, int shared_cu, hipStream_t s,
                            const CcmTune* t = nullptr, int layout = 0, int64_t kstride = 0,
                            int ksplit = 1);
+// the same with a shorter last chunk of each stride
+hipError_t launch_ccm_mfma(const BeamPtrs& bp, int nbeam, int nchan, int64_t row_stride,
+                           int64_t t0, int L, int nsub, int32_t* sum_x, int32_t* sum_xy,
+                           int32_t* count, int accumulate, int shared_cu, hipStream_t s,
+                           const CcmTune* t, int layout, int64_t kstride, int ksplit, int Llast);
 // Sums layouts: 0 = the C ABI's rows (sum_x[b][cell], sum_xy[pair][cell]);
 // 1 = one record per cell, sum_x[cell * (nbeam + npair) + row] with rows b
 // then nbeam + pair (sum_xy unused): what a one-cell-per-wave consumer reads

@@ -78,6 +78,18 @@ def test_long_sums_bit_exact(dev, nb, nchan, L, nsub, t0):
         assert S2[0, 0, 0, 0] > 2 ** 31         # past the int32 range
 
 
+@pytest.mark.parametrize("nb,nchan,L,nsub,t0", [
+    (19, 5, 64513, 1, 2), (19, 70, 64512, 2, 0), (5, 130, 50001, 3, 1), (36, 33, 33057, 1, 0)])
+def test_long_sums_last_chunk(dev, nb, nchan, L, nsub, t0):
+    """The last chunk of a sub-interval is shorter than the others, down to one sample, or equal
+    when whole 32-sample steps would leave it empty. Integers: exact."""
+    x = _data(nb, t0 + nsub * L + 3, nchan, nb + L)
+    _, _, sums, cnt = _long_sums(dev, x, L, nsub, t0, nchan)
+    S, S2 = ccm.sums_fp64(x, L, nsub, t0)
+    assert np.array_equal(sums.cpu().numpy(), _packed(S, S2))
+    assert (cnt.cpu().numpy() == L).all()
+
+
 @pytest.mark.parametrize("nb,nchan,L,nsub", [(19, 24, 40960, 2), (7, 9, 203450, 1),
                                               (72, 4, 81920, 1)])
 def test_long_eigen(dev, nb, nchan, L, nsub):

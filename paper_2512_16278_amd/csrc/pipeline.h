@@ -42,7 +42,7 @@ struct PipeEvents {
 };
 
 // Enqueue sums + eigen stage for pl.nsub sub-intervals starting at t0, in
-// groups, on s and ev.aux; later work on s waits for all of it. Rows of the
+// groups, on s and (more than one group) ev.aux; later work on s waits for all of it. Rows of the
 // per-cell outputs: stat/status[cell], eigvals/v1[i * out_stride + cell].
 hipError_t enqueue_eig_groups(const BeamPtrs& bp, int64_t row_stride, int64_t t0, int L,
                               const ProcessPlan& pl, double* stat, uint8_t* status,

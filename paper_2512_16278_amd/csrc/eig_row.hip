@@ -28,8 +28,8 @@
 // instead of a reciprocal and three, rescaled every eight steps).
 //
 // Bound: FP64 instruction issue, at two to three wavefronts per SIMD. 36 beams, 39000
-// cells with eigenvalues and vectors: @P36@; 19 beams, raw moments, 40960
-// cells: @NC@ (one wavefront per cell with the matrix on an 8 x 8 lane grid and
+// cells with eigenvalues and vectors: 5290 -> 1196 us; 19 beams, raw moments, 40960
+// cells: 407 -> 117 us (one wavefront per cell with the matrix on an 8 x 8 lane grid and
 // the vectors in LDS: 5290 us and 407 us).
 #include <math.h>
 

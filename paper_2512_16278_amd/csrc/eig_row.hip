@@ -27,10 +27,10 @@
 // P_i = (x - alpha_i) P_{i-1} - off_{i-1}^2 P_{i-2} (two multiply-adds per step
 // instead of a reciprocal and three, rescaled every eight steps).
 //
-// Bound: FP64 instruction issue, at two to three wavefronts per SIMD. 36 beams, 39000
-// cells with eigenvalues and vectors: 5290 -> 1196 us; 19 beams, raw moments, 40960
-// cells: 407 -> 117 us (one wavefront per cell with the matrix on an 8 x 8 lane grid and
-// the vectors in LDS: 5290 us and 407 us).
+// Bound: FP64 instruction issue, at two to three wavefronts per SIMD. 36 beams,
+// 39000 cells with eigenvalues and vectors: 5290 -> 1196 us; 19 beams, raw
+// moments, 40960 cells: 407 -> 117 us (before: one wavefront per cell with the
+// matrix on an 8 x 8 lane grid and the vectors in LDS).
 #include <math.h>
 
 #include "internal.h"

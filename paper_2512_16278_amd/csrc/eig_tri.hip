@@ -24,9 +24,9 @@
 //    transformation.
 //
 // Bound: FP64 instruction issue at two wavefronts per SIMD. 72 beams, 40960
-// cells: 2536 -> 2070 us (with the matrix on an 8 x 8 lane grid and every vector read
-// from LDS in both of its forms, about 70 LDS reads per step instead of 10:
-// 2536 us).
+// cells: 2536 -> 2070 us (before: the matrix on an 8 x 8 lane grid and every
+// vector read from LDS in both of its forms, about 70 LDS reads per step instead
+// of 10).
 #include <math.h>
 
 #include "internal.h"

@@ -35,6 +35,7 @@ struct ItemPlan {
   int nbeam, nchan;
   int64_t ncell;
   CcmClass cc;
+  long long first_key;       // the class of a launch of any size
   CcmTune ct;              // sums-engine choices of the item's shape class
   int solver, precision;   // eigen class (solver, precision)
   int lane_cls;            // template class of the per-lane or per-wave tridiagonal solver
@@ -120,7 +121,7 @@ rfi_status plan_batch(int nitem, const rfi_batch_item* items, const rfi_batch_pa
     ip.ncell = (int64_t)it.nsub * it.blk->nchan;
     ip.ct = CcmTune{te ? te->ccm_tile : 0, te ? te->ccm_stages : 0, te ? te->ccm_group_bytes : 0};
     if ((st = check_tune_entry(te, ip.nbeam, who)) != RFI_OK) return st;
-    if (ccm_class(ip.nbeam, &ip.cc, &ip.ct) != hipSuccess)
+    if (ccm_class(ip.nbeam, &ip.cc, &ip.ct, INT64_MAX, it.L) != hipSuccess)
       return fail(RFI_E_INVALID, "%s: item %d: no sums instance for %d beams", who, i, ip.nbeam);
     // long sub-intervals: the FP64 tridiagonal solver on the int64 sums (as
     // rfi_process_block; their cells read n L > 66,050 bytes each)
@@ -147,6 +148,22 @@ rfi_status plan_batch(int nitem, const rfi_batch_item* items, const rfi_batch_pa
                   "of a stream in separate batches", who);
   }
   // classes
+  // which of the sums engines: by the size of the launch that the items of an
+  // instance would form together
+  std::map<long long, std::pair<int64_t, int>> size;      // cells, longest L
+  for (int pass = 0; pass < 2; ++pass)
+    for (ItemPlan& ip : bpn->plans) {
+      if (ip.longL) continue;
+      if (pass == 0) {
+        ip.first_key = ip.cc.key;
+        size[ip.first_key].first += ip.ncell;
+        size[ip.first_key].second = std::max(size[ip.first_key].second, items[ip.idx].L);
+      } else {
+        (void)ccm_class(ip.nbeam, &ip.cc, &ip.ct, size[ip.first_key].first,
+                        size[ip.first_key].second);
+        ip.ct.engine = ip.cc.engine;
+      }
+    }
   std::map<long long, std::vector<int>> ccm;
   // (solver template class or 0, solver, precision, workgroup)
   std::map<std::tuple<int, int, int, int>, std::vector<int>> eig;
@@ -535,7 +552,8 @@ rfi_status rfi_tune_batch(int32_t nitem, const rfi_batch_item* items, const rfi_
     std::vector<long long> seen;
     {
       rfi::CcmClass c0;
-      if (rfi::ccm_class(kv.second.empty() ? 19 : max_nbeam[sc], &c0, nullptr) == hipSuccess)
+      if (rfi::ccm_class(kv.second.empty() ? 19 : max_nbeam[sc], &c0, nullptr, 1 << 20, 1024) ==
+          hipSuccess)
         seen.push_back(c0.key);
     }
     for (int tile = 0; tile < rfi::ccm_tile_variants(max_nbeam[sc]); ++tile) {
@@ -545,7 +563,7 @@ rfi_status rfi_tune_batch(int32_t nitem, const rfi_batch_item* items, const rfi_
         e.ccm_stages = stages;
         rfi::CcmTune ct{tile, stages, 0};
         rfi::CcmClass cc;
-        if (rfi::ccm_class(max_nbeam[sc], &cc, &ct) != hipSuccess) continue;
+        if (rfi::ccm_class(max_nbeam[sc], &cc, &ct, 1 << 20, 1024) != hipSuccess) continue;
         if (std::find(seen.begin(), seen.end(), cc.key) != seen.end()) continue;
         seen.push_back(cc.key);
         const float t = measure(e, 0, 4.f * best_ccm);

@@ -45,11 +45,12 @@ int max_split(int nsub, int nchan) {
 // pass of 42 us, 4 chunks (3 rounds) 1826 and 17 us.
 int split_for(int L, int nsub, int nchan, int nbeam, const CcmTune* t) {
   const int need = (L + RFI_MAX_COUNT - 1) / RFI_MAX_COUNT;
+  const int most = max_split(nsub, nchan) < L / 256 ? max_split(nsub, nchan) : L / 256;
   CcmClass cc;
-  if (ccm_class(nbeam, &cc, t) != hipSuccess) return need;
+  if (ccm_class(nbeam, &cc, t, (int64_t)nsub * nchan * most, RFI_MAX_COUNT) != hipSuccess)
+    return need;
   const int64_t ntiles = (int64_t)nsub * ((nchan + cc.cw - 1) / cc.cw);
   const int rows = 1 + (nbeam + 1) / 2;       // record rows per beam
-  const int most = max_split(nsub, nchan) < L / 256 ? max_split(nsub, nchan) : L / 256;
   int best = need;
   int64_t best_cost = INT64_MAX;
   for (int p = need; p <= most || p == need; ++p) {

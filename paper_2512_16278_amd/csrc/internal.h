@@ -34,6 +34,7 @@ struct CcmItem {
 // tiles given to one XCD in turn.
 struct CcmTune {
   int tile, stages, group_bytes;
+  int engine = 0;      // 0 = by the launch's size; 1 = whole blocks; 2 = packed
 };
 int ccm_tile_variants(int nbeam);
 // Instance class of the MFMA sums engine for a beam count: blocks of one
@@ -41,8 +42,10 @@ int ccm_tile_variants(int nbeam);
 struct CcmClass {
   long long key;
   int cw, nh, group_bytes, slots;   // slots: workgroups of the class the chip holds
+  int engine;
 };
-hipError_t ccm_class(int nbeam, CcmClass* c, const CcmTune* t = nullptr);
+// cells, L: of the whole launch (its cells, its longest sub-interval).
+hipError_t ccm_class(int nbeam, CcmClass* c, const CcmTune* t, int64_t cells, int L);
 // Batched sums launch over the items of one class (items in device memory,
 // sorted by wg0); nbeam_of_class is any member's beam count, t its choices;
 // parts: some item has more than one workgroup per tile.

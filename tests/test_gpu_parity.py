@@ -133,6 +133,37 @@ def test_ccm_time_parts(dev, nbeam, nchan, L):
         assert (dcnt.cpu().numpy() == 2 * L).all()
 
 
+@pytest.mark.parametrize("nbeam,nchan,nsub,L", [
+    (16, 6150, 8, 31), (19, 6170, 8, 33), (18, 6144, 8, 16), (32, 2050, 4, 48), (35, 4111, 2, 17),
+    (36, 2064, 4, 300), (39, 4100, 2, 1), (40, 2049, 4, 65), (48, 1030, 4, 33), (52, 4097, 1, 80),
+    (56, 2050, 2, 47), (64, 1040, 4, 32), (67, 4100, 1, 50), (71, 2050, 2, 15), (72, 1027, 4, 270)])
+def test_ccm_packed(dev, nbeam, nchan, nsub, L):
+    """Launches that fill the chip at 16 k to 16 k + 8 beams: every instance, ragged channel tiles,
+    stages that end in the first or second half of a step, a last round in parts, sums by rows
+    (then accumulated on top of themselves) and by cell records. Integers: exact."""
+    import torch
+    from paper_2512_16278_amd import rfi
+    rng = np.random.default_rng(nbeam * 7 + nchan + L)
+    x = rng.integers(0, 256, size=(nbeam, nsub * L + 1, nchan), dtype=np.uint8)
+    x[:, :L // 2 + 1, ::3] = rng.choice([0, 255], size=(nbeam, L // 2 + 1, (nchan + 2) // 3))
+    S, S2 = ccm.sums_fp64(x, L, nsub, t0=1)
+    rsx, rsxy = packed_oracle_sums(S, S2)
+    say("ccm packed", nbeam, nchan, nsub, L)
+    sx, sxy, cnt, (buf, blk, dsx, dsxy, dcnt) = run_ccm(x, L, nsub, dev, 1, t0=1)
+    assert np.array_equal(sx, rsx) and np.array_equal(sxy, rsxy) and (cnt == L).all()
+    rfi.rfi_ccm_accumulate(blk, 1, L, nsub, dsx, dsxy, dcnt, accumulate=1, variant=1)
+    torch.cuda.synchronize()
+    assert np.array_equal(dsx.cpu().numpy(), 2 * rsx)
+    assert np.array_equal(dsxy.cpu().numpy(), 2 * rsxy)
+    assert (dcnt.cpu().numpy() == 2 * L).all()
+    rec = torch.full((nsub * nchan, len(rsx) + len(rsxy)), -7, dtype=torch.int64, device=dev)
+    ws = torch.empty(rfi.rfi_ccm_long_workspace_size(nbeam, nchan, nsub), dtype=torch.uint8,
+                     device=dev)
+    rfi.rfi_ccm_accumulate_long(blk, 1, L, nsub, rec, dcnt, ws)
+    torch.cuda.synchronize()
+    assert np.array_equal(rec.cpu().numpy(), np.concatenate([rsx, rsxy]).T)
+
+
 def test_ccm_accumulate_across_calls(dev):
     import torch
     from paper_2512_16278_amd import rfi

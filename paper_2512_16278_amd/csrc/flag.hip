@@ -35,7 +35,8 @@
 //     its capacity falls back to a pass over every cell, so the result never
 //     depends on the prediction, only the time does;
 //  4. mask (many workgroups): mask = eligible and q > T.
-// A batched form runs the same four launches over many blocks at once.
+// A block of at most 16384 cells takes one launch, the iteration with all cells in
+// its list. A batched form runs the same launches over many blocks at once.
 #include <math.h>
 
 #include <algorithm>
@@ -54,6 +55,7 @@ constexpr int kSample = kPlanThreads * kPlanPer;
 constexpr int kIterThreads = 512;
 constexpr int kIterLoad = 16;                // tail entries per iterate thread and load batch
 constexpr int kNearMax = 16384;              // near-threshold tail entries kept in LDS
+constexpr int kAllLoad = 4;                  // cells per thread and load batch of a one-launch clip
 constexpr int kGridThreads = 256;
 constexpr int kChunkPer = 4;                 // cells per thread and chunk (scan, mask)
 constexpr int kChunk = kGridThreads * kChunkPer;
@@ -581,6 +583,10 @@ struct RedSplit {
   uint32_t n[NT / 64];
   uint64_t a[NT / 64], h2[NT / 64], hl[NT / 64], l2[NT / 64];
 };
+// Whether q fits the 64-bit split sums (acc_split).
+__device__ __forceinline__ bool fits_split(int64_t q) {
+  return (uint64_t)q < ((uint64_t)1 << 42);
+}
 __device__ __forceinline__ void acc_split(int64_t q, SplitSums& t) {
   const uint64_t qh = (uint64_t)q >> 21, ql = (uint64_t)q & ((1u << 21) - 1);
   t.n += 1;
@@ -789,8 +795,13 @@ __global__ __launch_bounds__(kGridThreads) void clip_scan_kernel(ClipJob job0, c
   }
 }
 
-// 3. iterate: the exact clip (one workgroup per block).
-template <bool kBatch>
+// 3. iterate: the exact clip (one workgroup per block). With kAll it is the only
+// launch, for a block whose cells fit its LDS list: it loads them itself, the band
+// is everything, and the mask is written from the list. Bound there: latency (the
+// load, then two barriers and a fit per iteration); the launches before and after
+// cost such a block more than the clip. 1024 cells: 11 us (four launches 34 us);
+// 12288 cells 18 us (38 us).
+template <bool kBatch, bool kAll>
 __global__ __launch_bounds__(kIterThreads) void clip_iter_kernel(ClipJob job0, const ClipJob* jobs) {
   const ClipJob J = job_of<kBatch>(job0, jobs, blockIdx.x);
   __shared__ Red3<kIterThreads> red;
@@ -800,41 +811,68 @@ __global__ __launch_bounds__(kIterThreads) void clip_iter_kernel(ClipJob job0, c
   __shared__ double sfit[3];
   const int64_t ncell = (int64_t)J.nsub * J.nchan;
   Ctrl* ct = ctrl_of(J);
-  // totals and the sums above the band, from the scan's partials
+  // totals and the sums above the band
   int64_t Nt = 0, Nf = 0;
   u128 Q1t = 0, Q2t = 0, F1 = 0, F2 = 0;
-  for (int w = threadIdx.x; w < J.nparts; w += kIterThreads) {
-    const Part p = parts_of(J)[w];
-    Nt += p.n;
-    Q1t += mk128(p.q1[0], p.q1[1]);
-    Q2t += mk128(p.q2[0], p.q2[1]);
-    Nf += p.nf;
-    F1 += mk128(p.f1[0], p.f1[1]);
-    F2 += mk128(p.f2[0], p.f2[1]);
-  }
-  block_sum3<kIterThreads>(Nt, Q1t, Q2t, red);
-  block_sum3<kIterThreads>(Nf, F1, F2, red);
-  const int64_t L = ct->L, H = ct->H;
-  const unsigned long long cnt = ct->count;
-  const bool complete = cnt <= (unsigned long long)J.tail_cap;
-  const int64_t M = complete ? (int64_t)cnt : 0;
-  const bool in_lds = M <= kNearMax;
-  // every listed q lies in (L, H]: the 64-bit split sums are exact when
-  // 0 <= q < 2^42 and at most 2^14 cells are summed
-  const bool split = L >= -1 && H < ((int64_t)1 << 42) && kNearMax <= (1 << 14);
+  int64_t L = INT64_MIN, H = INT64_MAX, M = ncell;
+  bool complete = true, in_lds = true, split;
   const int64_t* tail = tail_of(J);
-  if (complete && in_lds) {
-    for (int64_t k0 = 0; k0 < M; k0 += (int64_t)kIterThreads * kIterLoad) {
-      int64_t v[kIterLoad];
+  if constexpr (kAll) {
+    // a cell that takes no part is listed as INT64_MIN: above no threshold
+    bool fit = true;
+    for (int64_t k0 = 0; k0 < ncell; k0 += (int64_t)kIterThreads * kAllLoad) {
+      CellLd x[kAllLoad];
 #pragma unroll
-      for (int i = 0; i < kIterLoad; ++i) {
+      for (int i = 0; i < kAllLoad; ++i)
+        x[i] = load_cell(J, k0 + threadIdx.x + (int64_t)i * kIterThreads, ncell);
+#pragma unroll
+      for (int i = 0; i < kAllLoad; ++i) {
         const int64_t k = k0 + threadIdx.x + (int64_t)i * kIterThreads;
-        v[i] = tail[k < M ? k : 0];
+        if (k >= ncell) continue;
+        const bool ok = elig(x[i]);
+        const int64_t q = ok ? quant(x[i].s) : INT64_MIN;
+        if (ok) acc(q, Nt, Q1t, Q2t);
+        fit = fit && (!ok || fits_split(q));
+        near[k] = q;
       }
+    }
+    split = __syncthreads_and(fit) && kNearMax <= (1 << 14);
+    block_sum3<kIterThreads>(Nt, Q1t, Q2t, red);
+  } else {
+    // from the scan's partials
+    for (int w = threadIdx.x; w < J.nparts; w += kIterThreads) {
+      const Part p = parts_of(J)[w];
+      Nt += p.n;
+      Q1t += mk128(p.q1[0], p.q1[1]);
+      Q2t += mk128(p.q2[0], p.q2[1]);
+      Nf += p.nf;
+      F1 += mk128(p.f1[0], p.f1[1]);
+      F2 += mk128(p.f2[0], p.f2[1]);
+    }
+    block_sum3<kIterThreads>(Nt, Q1t, Q2t, red);
+    block_sum3<kIterThreads>(Nf, F1, F2, red);
+    L = ct->L;
+    H = ct->H;
+    const unsigned long long cnt = ct->count;
+    complete = cnt <= (unsigned long long)J.tail_cap;
+    M = complete ? (int64_t)cnt : 0;
+    in_lds = M <= kNearMax;
+    // every listed q lies in (L, H]: the 64-bit split sums are exact when
+    // 0 <= q < 2^42 and at most 2^14 cells are summed
+    split = L >= -1 && H < ((int64_t)1 << 42) && kNearMax <= (1 << 14);
+    if (complete && in_lds) {
+      for (int64_t k0 = 0; k0 < M; k0 += (int64_t)kIterThreads * kIterLoad) {
+        int64_t v[kIterLoad];
 #pragma unroll
-      for (int i = 0; i < kIterLoad; ++i) {
-        const int64_t k = k0 + threadIdx.x + (int64_t)i * kIterThreads;
-        if (k < M) near[k] = v[i];
+        for (int i = 0; i < kIterLoad; ++i) {
+          const int64_t k = k0 + threadIdx.x + (int64_t)i * kIterThreads;
+          v[i] = tail[k < M ? k : 0];
+        }
+#pragma unroll
+        for (int i = 0; i < kIterLoad; ++i) {
+          const int64_t k = k0 + threadIdx.x + (int64_t)i * kIterThreads;
+          if (k < M) near[k] = v[i];
+        }
       }
     }
   }
@@ -941,8 +979,12 @@ __global__ __launch_bounds__(kIterThreads) void clip_iter_kernel(ClipJob job0, c
     __syncthreads();
     mu = sfit[0]; sigma = sfit[1]; thr = sfit[2];
   }
+  if constexpr (kAll) {
+    const int64_t T = sT;                 // settled before the last barrier
+    for (int64_t k = threadIdx.x; k < ncell; k += kIterThreads) J.mask[k] = near[k] > T ? 1 : 0;
+  }
   if (threadIdx.x == 0) {
-    ct->T = sT;
+    if constexpr (!kAll) ct->T = sT;
     if (J.out) {
       J.out->mu = mu;
       J.out->sigma = sigma;
@@ -1204,11 +1246,6 @@ __device__ __forceinline__ void seg_report(const SegArgs& a, int64_t g, const Se
   o.converged = st.converged;
   o.nflag = (st.Nelig < 0 ? 0 : st.Nelig) - st.N;
   o.nfit = st.N;
-}
-
-// Whether q fits the 64-bit split sums (acc_split).
-__device__ __forceinline__ bool fits_split(int64_t q) {
-  return (uint64_t)q < ((uint64_t)1 << 42);
 }
 
 // One wavefront per segment of at most 64 PER cells, held in registers.
@@ -1821,11 +1858,15 @@ ClipJob make_clip_job(int nsub, int nchan, const double* stat, const uint8_t* st
 
 hipError_t launch_clip(const ClipJob& j, hipStream_t s) {
   const int64_t ncell = (int64_t)j.nsub * j.nchan;
+  if (ncell <= kNearMax) {
+    hipLaunchKernelGGL((clip_iter_kernel<false, true>), dim3(1), dim3(kIterThreads), 0, s, j, nullptr);
+    return hipGetLastError();
+  }
   const unsigned nmask = (unsigned)((ncell + kChunk - 1) / kChunk);
   hipLaunchKernelGGL(clip_plan_kernel<false>, dim3(1), dim3(kPlanThreads), 0, s, j, nullptr);
   hipLaunchKernelGGL(clip_scan_kernel<false>, dim3((unsigned)j.nparts), dim3(kGridThreads), 0, s,
                      j, nullptr);
-  hipLaunchKernelGGL(clip_iter_kernel<false>, dim3(1), dim3(kIterThreads), 0, s, j, nullptr);
+  hipLaunchKernelGGL((clip_iter_kernel<false, false>), dim3(1), dim3(kIterThreads), 0, s, j, nullptr);
   if (nmask > 0)
     hipLaunchKernelGGL(clip_mask_kernel<false>, dim3(nmask), dim3(kGridThreads), 0, s, j, nullptr);
   return hipGetLastError();
@@ -1842,10 +1883,15 @@ hipError_t launch_clip_batch(const ClipJob* jobs, const ClipJob* host_jobs, int 
   }
   const unsigned nmask = (unsigned)((maxcell + kChunk - 1) / kChunk);
   ClipJob none{};
+  if (maxcell <= kNearMax) {
+    hipLaunchKernelGGL((clip_iter_kernel<true, true>), dim3((unsigned)n), dim3(kIterThreads), 0, s,
+                       none, jobs);
+    return hipGetLastError();
+  }
   hipLaunchKernelGGL(clip_plan_kernel<true>, dim3((unsigned)n), dim3(kPlanThreads), 0, s, none, jobs);
   hipLaunchKernelGGL(clip_scan_kernel<true>, dim3((unsigned)maxparts, (unsigned)n),
                      dim3(kGridThreads), 0, s, none, jobs);
-  hipLaunchKernelGGL(clip_iter_kernel<true>, dim3((unsigned)n), dim3(kIterThreads), 0, s, none, jobs);
+  hipLaunchKernelGGL((clip_iter_kernel<true, false>), dim3((unsigned)n), dim3(kIterThreads), 0, s, none, jobs);
   if (nmask > 0)
     hipLaunchKernelGGL(clip_mask_kernel<true>, dim3(nmask, (unsigned)n), dim3(kGridThreads), 0, s,
                        none, jobs);

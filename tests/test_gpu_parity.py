@@ -564,6 +564,34 @@ def test_flag_fallback_and_large_tail(dev):
         (ref.mu, ref.sigma, ref.thr, ref.iterations, ref.nflag)
 
 
+@pytest.mark.parametrize("n", [1, 2, 64, 1023, 1025, 5000, 16383, 16384, 16385])
+def test_flag_one_launch(dev, n):
+    """Blocks up to and around the largest one clipped in a single launch, also with values
+    outside the range of the split sums (below 0 and from 4 on), with pooled state and when no
+    iteration is left: equal to the oracle bit for bit."""
+    import torch
+    from paper_2512_16278_amd import rfi
+    rng = np.random.default_rng(n)
+    for wide in (False, True):
+        s = _synthetic_stat(rng, n, 0.05)
+        if wide:
+            s = s * 40.0 - 1.0
+        status = (rng.uniform(size=n) < 0.02).astype(np.uint8)
+        for kappa, max_iter in ((3.0, 50), (1.5, 50), (2.0, 2)):
+            mask, st = _flag_case(dev, s, status, 1, n, kappa, max_iter)
+            ref = clip.clip_iterative(s, status == 0, kappa, max_iter)
+            assert np.array_equal(mask, ref.mask), (wide, kappa)
+            for k in ("mu", "sigma", "thr", "iterations", "nflag"):
+                assert _same(st[k], getattr(ref, k)), (wide, kappa, k)
+    state = torch.zeros(len(bytes(rfi.rfi_stream_state())), dtype=torch.uint8, device=dev)
+    ost = clip.StreamState()
+    for i in range(2):
+        s = _synthetic_stat(rng, n, 0.03 * (i + 1))
+        mask, st = _flag_case(dev, s, np.zeros(n, np.uint8), 1, n, state=state)
+        ref = clip.clip_stream(ost, s, np.ones(n, bool))
+        assert np.array_equal(mask, ref.mask) and st["iterations"] == ref.iterations, i
+
+
 def test_flag_edge_cases(dev):
     # nothing eligible; a single cell; all-equal values
     for s, status in ((np.full(10, 0.3), np.ones(10, np.uint8)),

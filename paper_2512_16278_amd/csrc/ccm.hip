@@ -97,6 +97,7 @@ struct MfmaCfg {
                                  : LDS_MAX;
   static constexpr int STG_BYTES = LDS - STG_OFF;
   static constexpr int SLOTS = 256 * (LDS_MAX / LDS < 2 ? 1 : 2);  // workgroups the chip holds
+  static constexpr bool DIRECT = false;                // records staged in LDS
   static constexpr bool FITS = RING <= LDS_MAX && STG_BYTES >= STG_MIN;
 };
 
@@ -1042,12 +1043,15 @@ __global__ __launch_bounds__(256) void zero_items_kernel(const CcmItem* items) {
 // that leaves CUs idle, or whose last round does, shares the samples of the last
 // round's tiles out. Cost in chunks per slot: rounds x (chunks + epilogue), for
 // the shared ones with a zeroing launch and atomic stores in place of plain
-// ones; shared only for a gain of a fiftieth. 19 beams: 16 tiles of 1024 samples
-// in 8 parts 49 -> 20 us (and 3 us to zero).
+// ones; shared only for a gain of a fiftieth. epilogue: chunks that a shared one
+// costs, 12, or where records go straight to memory what the atomics of all
+// nbeam + npair rows cost at one per ns and CU (72 beams 34: 4096 channels x 700
+// samples, 128 tiles, in 2 parts 196 us, whole 143 us). 19 beams: 16 tiles of
+// 1024 samples in 8 parts 49 -> 20 us (and 3 us to zero).
 struct Share {
   int nwhole, parts;
 };
-Share ccm_share(int64_t ntiles, int L, int slots) {
+Share ccm_share(int64_t ntiles, int L, int slots, int epilogue) {
   const int nchunk = (L + TC - 1) / TC;
   const int64_t full = ntiles / slots, tail = ntiles - full * slots;
   Share sh{(int)ntiles, 1};
@@ -1055,7 +1059,7 @@ Share ccm_share(int64_t ntiles, int L, int slots) {
   int64_t best = (full + 1) * (nchunk + 8) * 49 / 50;
   for (int p = 2; p <= 32 && p * 4 <= nchunk; ++p) {
     const int64_t cost = full * (nchunk + 8) +
-                         (tail * p + slots - 1) / slots * ((nchunk + p - 1) / p + 12) + 4;
+                         (tail * p + slots - 1) / slots * ((nchunk + p - 1) / p + epilogue) + 4;
     if (cost < best) {
       best = cost;
       sh = Share{(int)(full * slots), p};
@@ -1076,7 +1080,7 @@ hipError_t launch_cfg(K kern, int nh, const BeamPtrs& bp, int nbeam, int nchan, 
   if (e != hipSuccess) return e;
   const int64_t ntiles = (int64_t)nsub * nct;
   const int G = group_tiles(C::WIDTH, group_bytes);
-  const Share sh = ksplit > 1 ? Share{(int)ntiles, 1} : ccm_share(ntiles, L, C::SLOTS);
+  const Share sh = ksplit > 1 ? Share{(int)ntiles, 1} : ccm_share(ntiles, L, C::SLOTS, C::DIRECT ? 6 + (nbeam + 3) * 3 / 8 : 12);
   if (sh.parts > 1 && !accumulate) {
     e = launch_zero(sum_x, sum_xy, nbeam, (int64_t)nsub * nchan,
                     (int64_t)(sh.nwhole / nct) * nchan, layout, s);
@@ -1139,10 +1143,10 @@ hipError_t pack_dispatch(int nbeam, Op& op) {
 // Whether a launch over `cells` (sub-interval, channel) cells of L samples takes
 // the packed engine. Its tiles are as wide or wider on fewer waves, so they have
 // to fill the chip (whole blocks -> packed, us):
-//   32..72 beams (16 k to 16 k + 8): 128 tiles. 36 beams x 1024 channels x 1024
-//     samples, 16 sub-intervals (256 tiles) 194 -> 124, 4 sub-intervals (64) 69 ->
-//     76; 72 beams 4 sub-intervals (128) 353 -> 231, one of 340 samples (32) 64 ->
-//     71.
+//   32..72 beams (16 k to 16 k + 8): 128 tiles, from 48 beams on 96. 36 beams x
+//     1024 channels x 1024 samples, 16 sub-intervals (256 tiles) 194 -> 124, 4
+//     sub-intervals (64) 69 -> 76; 72 beams 4 sub-intervals (128) 353 -> 220, 3 (96)
+//     272 -> 217, one of 340 samples (32) 64 -> 71.
 //   16..19 beams, where only the epilogues are overlapped (two workgroups per
 //     CU): 768 tiles. 19 beams x 4096 channels x 512 samples x 16 (1024) 161 ->
 //     135, 1024 x 1024 x 60 (960) 277 -> 254, 2000 x 1500 x 10 (320) 153 -> 190;
@@ -1154,7 +1158,7 @@ bool takes_pack(int nbeam, const CcmTune* t, int64_t cells, int L) {
   if (nbf < 1 || nbf > 4 || left > (nbf == 1 ? 3 : 8)) return false;
   if (t && t->engine == 2) return true;
   if (nbf == 1) return cells >= 768 * 64 && L <= 8192;
-  return cells >= 128 * (nbf == 2 ? 64 : 32);
+  return cells >= (nbf == 2 ? 128 * 64 : 96 * 32);
 }
 
 // The MFMA engine's instance for a beam count: 16-row blocks NB (including

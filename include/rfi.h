@@ -141,8 +141,9 @@ rfi_status rfi_ccm_accumulate_long(const rfi_block* blk /* host */, int64_t t0, 
  *  RFI_EIG_WAVE    cyclic Jacobi (round-robin parallel ordering), one cell per
  *                  wavefront in LDS, FP32 or FP64, any nbeam;
  *  RFI_EIG_TRIDIAG Householder reduction to tridiagonal form and Sturm
- *                  bisection (Golub & Van Loan Sec. 8.3-8.4), FP64, one cell per
- *                  wavefront with the matrix in registers, any nbeam: about
+ *                  bisection (Golub & Van Loan Sec. 8.3-8.4), FP64, four cells
+ *                  per wavefront up to 40 beams and one above, the matrix in
+ *                  registers, any nbeam: about
  *                  (4/3) n^3 flops per cell instead of 6 n^3 per Jacobi sweep.
  *  RFI_EIG_LANE_TRI Householder reduction and Sturm bisection in FP32, one
  *                  cell per lane in registers, nbeam <= 20 (about (4/3) n^3 flops
@@ -212,8 +213,8 @@ rfi_status rfi_eig_batched_long(int32_t nbeam, int32_t nsub, int32_t nchan, cons
  * baseline, the bandpass to subtract from every sample of the channel;
  * passes[k nbeam + b] (nullable) the passes taken. Inputs in the rows layout
  * of rfi_ccm_accumulate. workspace: rfi_bandpass_workspace_size bytes
- * (caller-owned, one call at a time). One thread per (beam, sub-interval):
- * the solve is sequential over the channels.
+ * (caller-owned, one call at a time). One workgroup per (beam, sub-interval):
+ * its threads reduce a chunk of channels each and share the rest of the solve.
  * Errors: RFI_E_INVALID for bad sizes, lam <= 0, ratio < 0, itermax < 1 or
  * NULL pointers. */
 size_t rfi_bandpass_workspace_size(int32_t nbeam, int32_t nchan, int32_t nsub);
@@ -369,7 +370,8 @@ rfi_status rfi_eigvec_flag(int32_t nbeam, int32_t nsub, int32_t nchan, const flo
  * sub-intervals of L samples that start at sample t0 of blk. Sub-intervals
  * are processed in groups of `group`: the sums of group g are formed on
  * `stream` while earlier groups are eigendecomposed on a library-owned
- * helper stream, and the sums of at most three groups live in the workspace
+ * helper stream (a block of one group runs on `stream` alone), and the sums of
+ * at most three groups live in the workspace
  * at once, so the workspace stays bounded for any block length. group = 0
  * takes the whole block as one group while its sums fit in 1 GiB (the
  * fastest schedule measured: the two stages contend for the same vector ALU
@@ -468,7 +470,8 @@ typedef struct {
  *  ccm_tile        sums tile variant, 0 .. rfi_ccm_tile_variants(nbeam) - 1
  *                  (16-31 beams: 0 = 64 channels on 16 waves, 1 = 64
  *                  channels on 8 waves, 2 = 32 channels on 8 waves; others:
- *                  0 only);
+ *                  0 only). 0 with ccm_stages 0 also leaves the library the
+ *                  choice of its packed tiles, by the size of the launch;
  *  ccm_stages      cap of the global-to-LDS load ring depth, 2..4;
  *  ccm_group_bytes contiguous row bytes of the tiles one XCD takes in turn
  *                  (16 .. 16384; default 1024);

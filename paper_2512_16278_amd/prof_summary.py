@@ -85,10 +85,12 @@ def traffic(fetch_csv: str, write_csv: str, out_json: str, out_md: str, command:
         return COPY_BYTES / (vals[0] * 1024.0) if vals else None
 
     fs, ws = copy_scale(f), copy_scale(w)
-    ccm_f = [v for n, g, v in f if "ccm_mfma_kernel" in n]
-    ccm_w = [v for n, g, v in w if "ccm_mfma_kernel" in n]
+    is_sums = lambda n: re.search(r"ccm_(mfma|pack)_kernel", n)          # noqa: E731
+    ccm_f = [v for n, g, v in f if is_sums(n)]
+    ccm_w = [v for n, g, v in w if is_sums(n)]
     rec = {
-        "kernel": "ccm_mfma_kernel", "source_sha256": source_hash(),
+        "kernel": next((short_name(n).split("<")[0] for n, g, v in f if is_sums(n)), None),
+        "source_sha256": source_hash(),
         "fetch_scale": fs, "write_scale": ws,
         "fetch_bytes": ccm_f[0] * 1024.0 * fs if ccm_f and fs else None,
         "write_bytes": ccm_w[0] * 1024.0 * ws if ccm_w and ws else None,
@@ -107,8 +109,8 @@ def traffic(fetch_csv: str, write_csv: str, out_json: str, out_md: str, command:
              f"KiB by WRITE_SIZE (scale {ws:.4f}).", "",
              "| dispatch | FETCH_SIZE KiB | WRITE_SIZE KiB | fetch bytes | write bytes |",
              "|---|---|---|---|---|"]
-    for (n, g, v), (_, _, u) in zip([x for x in f if "ccm_mfma" in x[0]],
-                                   [x for x in w if "ccm_mfma" in x[0]]):
+    for (n, g, v), (_, _, u) in zip([x for x in f if is_sums(x[0])],
+                                   [x for x in w if is_sums(x[0])]):
         lines.append(f"| `{short_name(n)}` | {v:.0f} | {u:.0f} | {v * 1024 * fs / 1e9:.3f} GB | "
                      f"{u * 1024 * ws / 1e9:.3f} GB |")
     lines += ["", f"Source SHA-256 of csrc/ccm.hip: `{rec['source_sha256']}`"]

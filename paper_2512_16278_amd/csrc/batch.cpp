@@ -49,7 +49,6 @@ struct ItemPlan {
 struct EigClass {
   int lane_cls, solver, precision, wg, max_nbeam;
   std::vector<int> items;  // indices into plans
-  bool v1 = false;         // some item asks for v1
 };
 
 struct CcmLaunchClass {
@@ -182,7 +181,6 @@ rfi_status plan_batch(int nitem, const rfi_batch_item* items, const rfi_batch_pa
                 std::get<3>(kv.first), 0, kv.second};
     for (int k : kv.second) {
       ec.max_nbeam = std::max(ec.max_nbeam, bpn->plans[k].nbeam);
-      if (items[bpn->plans[k].idx].v1) ec.v1 = true;
     }
     bpn->eig_classes.push_back(ec);
   }

@@ -172,13 +172,13 @@ ClipJob make_clip_job(int nsub, int nchan, const double* stat, const uint8_t* st
                       const uint8_t* protect_chan, double kappa, int max_iter,
                       rfi_stream_state* state, uint8_t* mask, rfi_flag_stats* out, void* ws,
                       int64_t tail_cap = 0);
-// The clip of one block (four launches on s).
+// The clip of one block (four launches on s; one for a small block).
 hipError_t launch_clip(const ClipJob& j, hipStream_t s);
 // The clips of n blocks: jobs in device memory, host_jobs the same
 // descriptors on the host (grid sizes).
 hipError_t launch_clip_batch(const ClipJob* jobs, const ClipJob* host_jobs, int n, hipStream_t s);
-// Clip scopes: scopes bit 1 = the global clip of g (the four-launch clip for
-// fit 0, a one-workgroup clip for the histogram fit 1), bit 2 = one clip per
+// Clip scopes: scopes bit 1 = the global clip of g (launch_clip for fit 0,
+// passes over many workgroups for the histogram fit 1), bit 2 = one clip per
 // channel, bit 4 = one clip per sub-interval; g.mask gets the union (zeroed
 // first when bit 1 is absent); chan_out [nchan] / sub_out [nsub] nullable.
 hipError_t launch_clip_scoped(const ClipJob& g, int scopes, int fit, rfi_flag_stats* chan_out,

@@ -1051,6 +1051,10 @@ __global__ __launch_bounds__(256) void zero_items_kernel(const CcmItem* items) {
 struct Share {
   int nwhole, parts;
 };
+template <class C>
+int shared_epilogue(int nbeam) {
+  return C::DIRECT ? 6 + (nbeam + 3) * 3 / 8 : 12;
+}
 Share ccm_share(int64_t ntiles, int L, int slots, int epilogue) {
   const int nchunk = (L + TC - 1) / TC;
   const int64_t full = ntiles / slots, tail = ntiles - full * slots;
@@ -1080,7 +1084,7 @@ hipError_t launch_cfg(K kern, int nh, const BeamPtrs& bp, int nbeam, int nchan, 
   if (e != hipSuccess) return e;
   const int64_t ntiles = (int64_t)nsub * nct;
   const int G = group_tiles(C::WIDTH, group_bytes);
-  const Share sh = ksplit > 1 ? Share{(int)ntiles, 1} : ccm_share(ntiles, L, C::SLOTS, C::DIRECT ? 6 + (nbeam + 3) * 3 / 8 : 12);
+  const Share sh = ksplit > 1 ? Share{(int)ntiles, 1} : ccm_share(ntiles, L, C::SLOTS, shared_epilogue<C>(nbeam));
   if (sh.parts > 1 && !accumulate) {
     e = launch_zero(sum_x, sum_xy, nbeam, (int64_t)nsub * nchan,
                     (int64_t)(sh.nwhole / nct) * nchan, layout, s);
@@ -1235,6 +1239,7 @@ struct Describe {
     out->cw = C::WIDTH;
     out->nh = nh;
     out->slots = C::SLOTS;
+    out->epilogue = shared_epilogue<C>(nbeam);
     return nh > 0 ? hipSuccess : hipErrorInvalidValue;
   }
 };
@@ -1346,16 +1351,6 @@ hipError_t ccm_class(int nbeam, CcmClass* c, const CcmTune* t, int64_t cells, in
   c->group_bytes = t ? t->group_bytes : 0;
   c->key = c->key * 65536 + (c->group_bytes & 0xFFFF);   // (instance, group)
   return e;
-}
-
-int ccm_item_parts(int L, int64_t share) {
-  // a workgroup takes at most half a slot's share of the launch, so that the
-  // items of long sub-intervals do not outlast the others
-  const int nchunk = (L + TC - 1) / TC;
-  const int64_t most = share / 2 > 8 ? share / 2 : 8;
-  if (nchunk <= most) return 1;
-  const int64_t p = (nchunk + most - 1) / most;
-  return (int)(p < 32 ? p : 32);
 }
 
 int ccm_chunks(int L) { return (L + TC - 1) / TC; }

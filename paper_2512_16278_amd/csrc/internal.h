@@ -43,6 +43,7 @@ struct CcmClass {
   long long key;
   int cw, nh, group_bytes, slots;   // slots: workgroups of the class the chip holds
   int engine;
+  int epilogue;        // chunks that the epilogue of a shared tile's workgroup costs
 };
 // cells, L: of the whole launch (its cells, its longest sub-interval).
 hipError_t ccm_class(int nbeam, CcmClass* c, const CcmTune* t, int64_t cells, int L);
@@ -51,10 +52,7 @@ hipError_t ccm_class(int nbeam, CcmClass* c, const CcmTune* t, int64_t cells, in
 // parts: some item has more than one workgroup per tile.
 hipError_t launch_ccm_batch(int nbeam_of_class, const CcmTune* t, const CcmItem* items,
                             int nitem, int total_wg, bool parts, hipStream_t s);
-// Workgroups per tile of an item of sub-intervals of L samples when a slot's
-// share of the whole launch is `share` chunks; chunks of L samples.
-int ccm_item_parts(int L, int64_t share);
-int ccm_chunks(int L);
+int ccm_chunks(int L);   // 32-sample chunks of L samples
 
 // Kernel launchers (return a HIP error code; arguments already validated).
 // kstride: samples from the start of one sub-interval to the next (0 = L:

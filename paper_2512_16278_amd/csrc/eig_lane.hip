@@ -349,6 +349,7 @@ __device__ __forceinline__ void jacobi_cell(const EigArgs& g, int64_t cell, cons
 // 150 us (with a test and a count per step, and every eigenvalue bisected from
 // the whole bracket).
 constexpr float kMinOff2 = 1e-36f;
+constexpr float kMinNorm2 = 1e-30f;
 template <int N>
 __device__ __forceinline__ int lane_sturm(const float (&dg)[N], const float (&e2)[N], int n,
                                           float x) {
@@ -463,7 +464,8 @@ __device__ __forceinline__ void lanetri_cell(const EigArgs& g, int64_t cell, con
     constexpr int k = RFI_CI(K);
     // reflector of (x0, x_{k+2}, ...) onto (mu, 0, ...): v0 = x0 - mu without
     // cancellation, beta = 2 v0^2 / (s2 + v0^2) = -v0 / mu; nothing to do
-    // (beta = 0, v = e_{k+1}) when the column is already reduced
+    // (beta = 0, v = e_{k+1}) when the column is already reduced, to 1e-15 of a
+    // matrix of size 1: below that the squares leave FP32's range
     float s2 = 0.f;
     static_for<k + 2, N>([&](auto I) {
       const float x = A[Sym<N>::idx(RFI_CI(I), k)];
@@ -474,7 +476,7 @@ __device__ __forceinline__ void lanetri_cell(const EigArgs& g, int64_t cell, con
     // hardware square root and reciprocals (about 1 ulp): the FP32 reduction
     // only has to span the subspace the FP64 Ritz pass refines
     const float mu = __builtin_amdgcn_sqrtf(mu2);
-    const bool refl = s2 > 0.f;
+    const bool refl = s2 > kMinNorm2;
     const float v0 = x0 <= 0.f ? x0 - mu : -s2 * __builtin_amdgcn_rcpf(x0 + mu);
     const float beta = refl ? -v0 * __builtin_amdgcn_rcpf(mu) : 0.f;
     const float iv0 = refl ? __builtin_amdgcn_rcpf(v0) : 0.f;

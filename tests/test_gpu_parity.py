@@ -354,6 +354,27 @@ def test_eig_tridiag_decoupled(dev, nbeam):
     assert (status == np.where(cr.degenerate.ravel(), 1, 0)).all()
 
 
+@pytest.mark.parametrize("nbeam", [2, 3, 4, 7, 8, 13, 16, 19, 20])
+def test_eig_lane_tri_decoupled(dev, nbeam):
+    """The per-lane Householder solver on correlation matrices that fall apart (zero off-diagonals
+    and exact zero pivots in the eigenvalue counts). FP32 eigenvalues: rounding of n operations of
+    size lambda_1 <= n, 2^-22 n; the statistic comes from the FP64 Ritz value."""
+    rng = np.random.default_rng(160 + nbeam)
+    L, nc = 128, 6
+    x = np.clip(np.rint(128 + 20 * rng.standard_normal((nbeam, L, nc))), 0, 255).astype(np.uint8)
+    x[:, :, 0] = x[0, :, 0]                     # all alike
+    x[1:, :, 1] = x[1, :, 1]                    # all alike but beam 0
+    x[nbeam // 2:, :, 2] = 77                   # half of them dead
+    x[1:, :, 3] = 5                             # one alive
+    x[:, :, 4] = 9                              # none
+    stat, status, ev, _ = _eig_case(dev, x, L, 1, 32, 4)
+    cr = pipeline.cells(x, L, 1)
+    w = cr.w.reshape(nc, nbeam)
+    assert np.abs(ev.T - w).max() <= 2.0 ** -22 * nbeam * 4
+    assert np.abs(stat - cr.stat.ravel()).max() <= 1e-10
+    assert (status == np.where(cr.degenerate.ravel(), 1, 0)).all()
+
+
 def test_eig_tridiag_72_beams_many_cells(dev):
     """The 72-beam class at the shape the uneven batch runs (L = 512) over
     4200 cells, so that many workgroups and the XCD-contiguous cell order

@@ -206,8 +206,19 @@ __global__ __launch_bounds__(kRowThreads, (S == 1 ? 3 : 2)) void eig_row_kernel(
   });
   // a dead beam may belong to any lane of the row
   bool degenerate = (__ballot(dead) >> (threadIdx.x & 48) & 0xffff) != 0;
-  const double frob2 = NC ? group_sum<16>(dgsq) + 2.0 * group_sum<16>(offsq) : (double)n + 2.0 * group_sum<16>(offsq);
-  if constexpr (NC) degenerate = !(frob2 > 0.0);
+  double frob2 = NC ? group_sum<16>(dgsq) + 2.0 * group_sum<16>(offsq)
+                    : (double)n + 2.0 * group_sum<16>(offsq);
+  int scale = 0;                                       // the matrix held is M 2^-scale
+  if constexpr (NC) {
+    degenerate = !(frob2 > 0.0);
+    scale = unit_scale(frob2);
+    const double sc = ldexp(1.0, -scale);
+    static_for<0, N>([&](auto J_) {
+      constexpr int j = RFI_CI(J_);
+      static_for<0, S>([&](auto A_) { A[RFI_CI(A_)][j] *= sc; });
+      if constexpr (j < E) B[j] *= sc;
+    });
+  }
   __syncthreads();                                     // the staged sums have been read
 
   // the cell's tridiagonal in LDS, over the staged sums
@@ -315,7 +326,7 @@ __global__ __launch_bounds__(kRowThreads, (S == 1 ? 3 : 2)) void eig_row_kernel(
   });
   wave_sync();
 
-  // the non-centred matrix has the scale of the data, so its stops are relative
+  // the non-centred matrix has no eigenvalue of order 1 that its stops could lean on
   constexpr double kFloor = NC ? 1e-300 : 1.0;
   const Spectrum sp = spectrum_bounds<16>(ae, off, n, l);
   const double lam1 = largest_eigenvalue<16>(ae, n, l, sp, kFloor);
@@ -347,7 +358,7 @@ __global__ __launch_bounds__(kRowThreads, (S == 1 ? 3 : 2)) void eig_row_kernel(
           const double lj = fabs(z[j]);
           rank += (lj > li) || (lj == li && j > i);
         }
-        g.eigvals[rank * g.out_stride + cell] = bad ? 0.f : (float)ev[s];
+        g.eigvals[rank * g.out_stride + cell] = bad ? 0.f : (float)(NC ? ldexp(ev[s], scale) : ev[s]);
       }
     }
     wave_sync();

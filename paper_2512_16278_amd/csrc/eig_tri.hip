@@ -217,9 +217,18 @@ __global__ __launch_bounds__(64, N <= 48 ? 3 : 2) void eig_tri_kernel(
   });
   int degenerate = __any(dead);
   const double off2 = group_sum<64>(offsq) + group_sum<16>(offe);
-  const double frob2 = NC ? group_sum<64>(dgsq) + group_sum<16>(dge) + 2.0 * off2
-                          : (double)n + 2.0 * off2;
-  if constexpr (NC) degenerate = !(frob2 > 0.0);
+  double frob2 = NC ? group_sum<64>(dgsq) + group_sum<16>(dge) + 2.0 * off2
+                    : (double)n + 2.0 * off2;
+  int scale = 0;                           // the matrix held is M 2^-scale
+  if constexpr (NC) {
+    degenerate = !(frob2 > 0.0);
+    scale = unit_scale(frob2);
+    const double sc = ldexp(1.0, -scale);
+    static_for<0, N>([&](auto J_) {
+      A[RFI_CI(J_)] *= sc;
+      if constexpr (RFI_CI(J_) < E) B[RFI_CI(J_)] *= sc;
+    });
+  }
   wave_sync();                             // the staged sums have been read
 
   double2* const ae = (double2*)lds;       // (alpha_i, off_{i-1}^2)
@@ -358,7 +367,7 @@ __global__ __launch_bounds__(64, N <= 48 ? 3 : 2) void eig_tri_kernel(
         const double lj = fabs(z[j]);
         rank += (lj > li) || (lj == li && j > i);
       }
-      g.eigvals[rank * g.out_stride + cell] = (float)ev[s];
+      g.eigvals[rank * g.out_stride + cell] = (float)(NC ? ldexp(ev[s], scale) : ev[s]);
     }
     wave_sync();
   }

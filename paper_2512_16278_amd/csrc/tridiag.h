@@ -206,6 +206,17 @@ __device__ __forceinline__ double rcp2(double x) {
   return fma(r, fma(-x, r, 1.0), r);
 }
 
+// The power of two that brings a matrix of squared norm frob2 to a norm of about
+// 1 when divided out, and frob2 with it (an exact step). The minors below multiply
+// up to eight of a matrix's entries before they are rescaled, which leaves FP64's
+// range outside 1e-36 .. 1e36: a correlation matrix is always inside, the
+// non-centred matrix of a blanked band (its baseline decays to 1e-20 and less) not.
+__device__ __forceinline__ int unit_scale(double& frob2) {
+  const int e = __builtin_amdgcn_frexp_exp(frob2) >> 1;
+  frob2 = ldexp(frob2, -2 * e);
+  return e;
+}
+
 // orders this wavefront's LDS accesses among its lanes
 __device__ __forceinline__ void wave_sync() {
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");

@@ -258,6 +258,51 @@ def test_noncentred_degenerate_and_bad_count(dev):
     assert (st[1] & 16).all() and ((st[[0, 2]] & 16) == 0).all()
 
 
+@pytest.mark.parametrize("nb", [3, 19, 24, 36, 44, 72, 79])
+def test_noncentred_scale(dev, nb):
+    """The statistic does not depend on the scale of the power: M = z z^T of zero samples, |z| from
+    1e-60 to 1e60, has statistic 1, the one eigenvalue |z|^2 and the vector z / |z|."""
+    import torch
+    from paper_2512_16278_amd import rfi
+    rng = np.random.default_rng(nb)
+    F, scales = 9, np.array([1e-60, 1e-25, 1e-20, 1e-12, 1.0, 1e15, 1e20, 1e40, 1e60])
+    z = rng.uniform(0.5, 1.5, (nb, F)) * scales[None, :]
+    sx, sxy, cnt = sums_buffers(nb, 1, F, dev)
+    sx.zero_()
+    sxy.zero_()
+    cnt.fill_(64)
+    s, st, ev, v1 = _noncentred(dev, nb, 1, F, sx, sxy, cnt, torch.from_numpy(z).to(dev))
+    assert (st == 0).all()
+    assert np.abs(s - 1.0).max() <= 1e-12
+    lam = (z * z).sum(axis=0)
+    fp32 = (lam > 1e-37) & (lam < 1e38)               # the eigenvalues are FP32 outputs
+    assert fp32.sum() >= 2
+    assert np.abs(ev[0] / lam - 1.0)[fp32].max() <= 1e-6
+    assert (np.abs(ev[1:]) / lam)[:, fp32].max() <= 1e-6
+    assert np.abs(v1 - z / np.sqrt(lam)).max() <= 1e-5
+
+
+def test_noncentred_blanked_band(dev):
+    """Channels without power beside a used band: the fitted baseline decays far below 1e-18
+    there, and the raw-moment statistic of those cells is still that of their matrix."""
+    import torch
+    from paper_2512_16278_amd import rfi
+    nb, nsub, F, L = 19, 1, 700, 512
+    x = _data(np.random.default_rng(77), nb, nsub * L, F)
+    x[:, :, 200:] = 0
+    _, sx, sxy, cnt = _gpu_sums(dev, x, L, nsub, F)
+    z = torch.empty((nb, nsub * F), dtype=torch.float64, device=dev)
+    rfi.rfi_bandpass_arpls(nb, nsub, F, sx, cnt, z, lam=1e3)
+    torch.cuda.synchronize()
+    zg = z.cpu().numpy().reshape(nb, nsub, F).transpose(1, 2, 0)
+    assert 0 < np.abs(zg[0, -1]).max() < 1e-19
+    s, st, _, _ = _noncentred(dev, nb, nsub, F, sx, sxy, cnt, z)
+    S, S2 = ccm.sums_fp64(x, L, nsub)
+    so, _ = bandpass.statistic_general(bandpass.noncentred_ccm(S, S2, L, zg))
+    assert (st == 0).all()
+    assert np.abs(s - so.ravel()).max() <= 1e-12
+
+
 def test_arpls_full_band(dev):
     """19 beams x 4096 channels (the FAST configuration), one sub-interval of
     1024 samples: every system on the GPU, beam 0 against the dense oracle

@@ -694,7 +694,7 @@ __global__ __launch_bounds__(kPlanThreads) void clip_plan_kernel(ClipJob job0, c
     Q2h = (double)mk128(J.state->q2[0], J.state->q2[1]) / (TWO40 * TWO40);
   }
   double T = INFINITY, sig = 0.0, prev = -1.0, T1 = INFINITY, sig1 = 0.0;
-  for (int it = 0; it < J.max_iter + 1; ++it) {
+  for (int it = 0; it <= J.max_iter; ++it) {
     double n = 0, a = 0, b = 0;
 #pragma unroll
     for (int i = 0; i < kPlanPer; ++i)
@@ -893,7 +893,7 @@ __global__ __launch_bounds__(kIterThreads) void clip_iter_kernel(ClipJob job0, c
   int64_t Nl = 0;                        // sums of the last fit (pooled)
   u128 Q1l = 0, Q2l = 0;
   double mu = NAN, sigma = NAN, thr = NAN;
-  for (int guard = 0; guard <= J.max_iter + 1; ++guard) {
+  for (int64_t guard = 0; guard <= (int64_t)J.max_iter + 1; ++guard) {
     __syncthreads();                      // thread 0's update of sT is visible
     const int64_t T = sT;
     __syncthreads();                      // every thread has read T before it changes
@@ -1954,7 +1954,7 @@ hipError_t launch_hist_all(const SegArgs& a, hipStream_t s) {
   HistCtl* ct = (HistCtl*)(a.mask + c0);
   const unsigned grid = (unsigned)std::min<int64_t>((ncell + kHistStep - 1) / kHistStep, kHistWG);
   // a clip of max_iter fits needs max_iter + 1 moment passes
-  const int nfit = std::min(kHistFits, a.max_iter + 1);
+  const int nfit = a.max_iter < kHistFits ? a.max_iter + 1 : kHistFits;
   hipLaunchKernelGGL(hist_init_kernel, dim3(1), dim3(256), 0, s, ct);
   for (int f = 0; f < nfit; ++f) {
     hipLaunchKernelGGL(hist_moments_kernel, dim3(grid), dim3(kGridThreads), 0, s, a, ct, f);

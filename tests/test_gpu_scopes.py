@@ -135,3 +135,32 @@ def test_scopes_segment_lengths(dev, K, F, fit):
                 _cmp(g, ref.chan[j], exact)
             for k, g in enumerate(_stats(so, K)):
                 _cmp(g, ref.sub[k], exact)
+
+
+@pytest.mark.parametrize("K,F", [(5, 100), (9, 2048)])
+def test_largest_max_iter(dev, K, F):
+    """max_iter up to the largest int32: as a cap that the clip does not reach (one launch and
+    four, the histogram fit in one workgroup and over many)."""
+    import torch
+    from paper_2512_16278_amd import rfi
+    rng = np.random.default_rng(K + F)
+    st = torch.from_numpy(_stat(rng, K, F).ravel().copy()).to(dev)
+    stt = torch.zeros(K * F, dtype=torch.uint8, device=dev)
+
+    def clipped(max_iter, fit):
+        mask = torch.full((K * F,), 9, dtype=torch.uint8, device=dev)
+        out = torch.zeros(48, dtype=torch.uint8, device=dev)
+        say("max_iter", K, F, max_iter, fit)
+        if fit is None:
+            rfi.rfi_flag(K, F, st, stt, mask, max_iter=max_iter, out=out)
+        else:
+            rfi.rfi_flag_scoped(K, F, st, stt, mask, scopes=1, fit=fit, max_iter=max_iter, out=out)
+        torch.cuda.synchronize()
+        return mask.cpu().numpy(), _stats(out, 1)[0]
+
+    for fit in (None, rfi.RFI_FIT_MOMENTS, rfi.RFI_FIT_HISTOGRAM):
+        m0, s0 = clipped(200, fit)
+        assert s0["converged"] and s0["iterations"] < 200 and 0 < m0.sum() < K * F
+        for most in (2 ** 31 - 2, 2 ** 31 - 1):
+            m1, s1 = clipped(most, fit)
+            assert np.array_equal(m0, m1) and s0 == s1, (most, fit)

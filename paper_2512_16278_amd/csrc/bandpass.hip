@@ -165,9 +165,13 @@ __global__ __launch_bounds__(T) void arpls_kernel(BpArgs a) {
 #pragma unroll
   for (int i = 0; i < m; ++i) w[i] = 1.0;
 
-  // reduced system, level by level: level l has T >> l blocks at offset
-  // 2 T - (2 T >> l); arrays A (3: a, b, d), E (4: coupling to the block
-  // before, row-major), r (2), each of 2 T doubles
+  // reduced system, level by level: level l has Tn >> l blocks at offset
+  // 2 Tn - (2 Tn >> l); arrays A (3: a, b, d), E (4: coupling to the block
+  // before, row-major), r (2), each of 2 T doubles. Tn (a power of two) covers the
+  // chunks that hold channels; the others' unit rows couple to nothing and their
+  // solution is not read (3 channels: no level instead of six).
+  int Tn = 1;
+  while (Tn * m < F) Tn <<= 1;
   auto arr = [&](int v) { return lds + (size_t)v * 2 * T; };
   double *Aa = arr(0), *Ab = arr(1), *Ad = arr(2), *E0 = arr(3), *E1 = arr(4), *E2 = arr(5),
          *E3 = arr(6), *R0 = arr(7), *R1 = arr(8);
@@ -251,7 +255,7 @@ __global__ __launch_bounds__(T) void arpls_kernel(BpArgs a) {
     // reduction: the odd blocks of a level survive, each absorbing its two
     // even neighbours
     int o = 0;
-    for (int n = T; n > 1; n >>= 1) {
+    for (int n = Tn; n > 1; n >>= 1) {
       const int on = o + n;
       if (t < n / 2) {
         const int s = o + 2 * t + 1, e = s - 1;
@@ -306,8 +310,8 @@ __global__ __launch_bounds__(T) void arpls_kernel(BpArgs a) {
     }
     __syncthreads();
     // back: the solution of each block replaces its right-hand side
-    for (int n = 2; n <= T; n <<= 1) {
-      const int oc = 2 * T - 2 * n, on = oc + n;
+    for (int n = 2; n <= Tn; n <<= 1) {
+      const int oc = 2 * Tn - 2 * n, on = oc + n;
       if (t < n / 2) {
         const int e = oc + 2 * t, s = e + 1;
         const double xs0 = R0[on + t], xs1 = R1[on + t];

@@ -1043,7 +1043,7 @@ __global__ __launch_bounds__(kGridThreads) void clip_mask_kernel(ClipJob job0, c
 //
 // Who clips a segment depends on its length m (seg_iterate below is the
 // iteration of all of them):
-//  - m <= 512: one wavefront, the cells in its registers (a sum or a fit needs
+//  - m <= 1024: one wavefront, the cells in its registers (a sum or a fit needs
 //    no barrier and no reload; four segments share a workgroup);
 //  - m <= 16384: one workgroup, the eligible cells kept in LDS;
 //  - longer: one workgroup re-reading its cells every pass, except the whole
@@ -1051,12 +1051,14 @@ __global__ __launch_bounds__(kGridThreads) void clip_mask_kernel(ClipJob job0, c
 //    workgroups (hist_moments_kernel, hist_bins_kernel).
 // 99 x 4096 cells, histogram fit: channels (99 cells) 26 us, sub-intervals
 // (4096 cells) 49 us, whole block 190 us over all its launches (one workgroup
-// per segment and a reload per pass: 169, 148 and 1985 us).
+// per segment and a reload per pass: 169, 148 and 1985 us). Moment fit, 600
+// segments of 700 cells: one wavefront 24 us, in LDS 52, reloaded 45; 99 of 1024:
+// 22, 33, 31.
 constexpr int kSegThreads = 256;      // four short segments, or one long one
 constexpr int kSegLdsThreads = 512;   // a segment kept in LDS
 constexpr int kSegThreadsAll = 1024;  // the whole block as one segment
 constexpr int kSegUnroll = 4;         // cells per thread whose loads are issued together
-constexpr int kSegWaveMax = 512;      // cells of a segment held by one wavefront
+constexpr int kSegWaveMax = 1024;     // cells of a segment held by one wavefront
 constexpr int kSegLdsMax = 16384;     // cells of a segment held in LDS
 constexpr int kBins = 64;
 
@@ -1920,6 +1922,8 @@ hipError_t launch_segments(const SegArgs& a, hipStream_t s) {
   const dim3 waves((unsigned)((nseg + kPer - 1) / kPer));
   if (m <= 128) {
     hipLaunchKernelGGL((segclip_wave_kernel<MODE, 2>), waves, dim3(kSegThreads), 0, s, a);
+  } else if (m <= 512) {
+    hipLaunchKernelGGL((segclip_wave_kernel<MODE, 8>), waves, dim3(kSegThreads), 0, s, a);
   } else if (m <= kSegWaveMax) {
     hipLaunchKernelGGL((segclip_wave_kernel<MODE, kSegWaveMax / 64>), waves, dim3(kSegThreads), 0,
                        s, a);

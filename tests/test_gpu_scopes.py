@@ -137,6 +137,13 @@ def test_scopes_segment_lengths(dev, K, F, fit):
                 _cmp(g, ref.sub[k], exact)
 
 
+@pytest.mark.parametrize("fit", ["moments", "histogram"])
+@pytest.mark.parametrize("K,F", [(1023, 9), (1024, 9), (1025, 9), (7, 700), (7, 1024), (7, 1025)])
+def test_scopes_longest_in_registers(dev, K, F, fit):
+    """Segments around the longest that one wavefront holds in registers (1024 cells)."""
+    test_scopes_segment_lengths(dev, K, F, fit)
+
+
 @pytest.mark.parametrize("K,F", [(5, 100), (9, 2048)])
 def test_largest_max_iter(dev, K, F):
     """max_iter up to the largest int32: as a cap that the clip does not reach (one launch and

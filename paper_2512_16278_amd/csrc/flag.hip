@@ -35,7 +35,7 @@
 //     its capacity falls back to a pass over every cell, so the result never
 //     depends on the prediction, only the time does;
 //  4. mask (many workgroups): mask = eligible and q > T.
-// A block of at most 16384 cells takes one launch, the iteration with all cells in
+// A block of at most 12288 cells takes one launch, the iteration with all cells in
 // its list. A batched form runs the same launches over many blocks at once.
 #include <math.h>
 
@@ -55,7 +55,8 @@ constexpr int kSample = kPlanThreads * kPlanPer;
 constexpr int kIterThreads = 512;
 constexpr int kIterLoad = 16;                // tail entries per iterate thread and load batch
 constexpr int kNearMax = 16384;              // near-threshold tail entries kept in LDS
-constexpr int kAllLoad = 4;                  // cells per thread and load batch of a one-launch clip
+constexpr int kAllMax = 12288;               // cells of a one-launch clip
+constexpr int kAllLoad = 4;                  // cells per thread and load batch of it
 constexpr int kGridThreads = 256;
 constexpr int kChunkPer = 4;                 // cells per thread and chunk (scan, mask)
 constexpr int kChunk = kGridThreads * kChunkPer;
@@ -799,8 +800,10 @@ __global__ __launch_bounds__(kGridThreads) void clip_scan_kernel(ClipJob job0, c
 // launch, for a block whose cells fit its LDS list: it loads them itself, the band
 // is everything, and the mask is written from the list. Bound there: latency (the
 // load, then two barriers and a fit per iteration); the launches before and after
-// cost such a block more than the clip. 1024 cells: 11 us (four launches 34 us);
-// 12288 cells 18 us (38 us).
+// cost such a block more than the clip, while every iteration reads all cells
+// again, so that the limit is set by the clips of many iterations. 1024 cells: 11
+// us (four launches 34 us); 12288 cells, 3 / 8 iterations: 23 / 46 us (32 / 47),
+// 16384 cells, 4 / 10 iterations: 31 / 64 us (34 / 53).
 template <bool kBatch, bool kAll>
 __global__ __launch_bounds__(kIterThreads) void clip_iter_kernel(ClipJob job0, const ClipJob* jobs) {
   const ClipJob J = job_of<kBatch>(job0, jobs, blockIdx.x);
@@ -1860,7 +1863,7 @@ ClipJob make_clip_job(int nsub, int nchan, const double* stat, const uint8_t* st
 
 hipError_t launch_clip(const ClipJob& j, hipStream_t s) {
   const int64_t ncell = (int64_t)j.nsub * j.nchan;
-  if (ncell <= kNearMax) {
+  if (ncell <= kAllMax) {
     hipLaunchKernelGGL((clip_iter_kernel<false, true>), dim3(1), dim3(kIterThreads), 0, s, j, nullptr);
     return hipGetLastError();
   }
@@ -1885,7 +1888,7 @@ hipError_t launch_clip_batch(const ClipJob* jobs, const ClipJob* host_jobs, int 
   }
   const unsigned nmask = (unsigned)((maxcell + kChunk - 1) / kChunk);
   ClipJob none{};
-  if (maxcell <= kNearMax) {
+  if (maxcell <= kAllMax) {
     hipLaunchKernelGGL((clip_iter_kernel<true, true>), dim3((unsigned)n), dim3(kIterThreads), 0, s,
                        none, jobs);
     return hipGetLastError();

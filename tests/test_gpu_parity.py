@@ -613,6 +613,12 @@ def test_flag_one_launch(dev, n):
         assert np.array_equal(mask, ref.mask) and st["iterations"] == ref.iterations, i
 
 
+@pytest.mark.parametrize("n", [12287, 12288, 12289])
+def test_flag_largest_one_launch(dev, n):
+    """Around the largest block that is clipped in a single launch."""
+    test_flag_one_launch(dev, n)
+
+
 def test_flag_edge_cases(dev):
     # nothing eligible; a single cell; all-equal values
     for s, status in ((np.full(10, 0.3), np.ones(10, np.uint8)),

@@ -37,6 +37,7 @@ struct ItemPlan {
   CcmClass cc;
   long long first_key;       // the class of a launch of any size
   int parts;                 // workgroups per tile of its sums
+  bool lined;                // its beams are lined up (ccm_lined_up)
   CcmTune ct;              // sums-engine choices of the item's shape class
   int solver, precision;   // eigen class (solver, precision)
   int lane_cls;            // template class of the per-lane or per-wave tridiagonal solver
@@ -121,7 +122,8 @@ rfi_status plan_batch(int nitem, const rfi_batch_item* items, const rfi_batch_pa
     ip.ncell = (int64_t)it.nsub * it.blk->nchan;
     ip.ct = CcmTune{te ? te->ccm_tile : 0, te ? te->ccm_stages : 0, te ? te->ccm_group_bytes : 0};
     if ((st = check_tune_entry(te, ip.nbeam, who)) != RFI_OK) return st;
-    if (ccm_class(ip.nbeam, &ip.cc, &ip.ct, INT64_MAX, it.L) != hipSuccess)
+    ip.lined = ccm_lined_up(ip.bp.p, ip.nbeam, it.blk->row_stride);
+    if (ccm_class(ip.nbeam, &ip.cc, &ip.ct, INT64_MAX, it.L, ip.lined) != hipSuccess)
       return fail(RFI_E_INVALID, "%s: item %d: no sums instance for %d beams", who, i, ip.nbeam);
     // long sub-intervals: the FP64 tridiagonal solver on the int64 sums (as
     // rfi_process_block; their cells read n L > 66,050 bytes each)
@@ -160,7 +162,7 @@ rfi_status plan_batch(int nitem, const rfi_batch_item* items, const rfi_batch_pa
         size[ip.first_key].second = std::max(size[ip.first_key].second, items[ip.idx].L);
       } else {
         (void)ccm_class(ip.nbeam, &ip.cc, &ip.ct, size[ip.first_key].first,
-                        size[ip.first_key].second);
+                        size[ip.first_key].second, ip.lined);
         ip.ct.engine = ip.cc.engine;
       }
     }
@@ -615,7 +617,7 @@ rfi_status rfi_tune_batch(int32_t nitem, const rfi_batch_item* items, const rfi_
     std::vector<long long> seen;
     {
       rfi::CcmClass c0;
-      if (rfi::ccm_class(kv.second.empty() ? 19 : max_nbeam[sc], &c0, nullptr, 1 << 20, 1024) ==
+      if (rfi::ccm_class(kv.second.empty() ? 19 : max_nbeam[sc], &c0, nullptr, 1 << 20, 1024, false) ==
           hipSuccess)
         seen.push_back(c0.key);
     }
@@ -626,7 +628,7 @@ rfi_status rfi_tune_batch(int32_t nitem, const rfi_batch_item* items, const rfi_
         e.ccm_stages = stages;
         rfi::CcmTune ct{tile, stages, 0};
         rfi::CcmClass cc;
-        if (rfi::ccm_class(max_nbeam[sc], &cc, &ct, 1 << 20, 1024) != hipSuccess) continue;
+        if (rfi::ccm_class(max_nbeam[sc], &cc, &ct, 1 << 20, 1024, false) != hipSuccess) continue;
         if (std::find(seen.begin(), seen.end(), cc.key) != seen.end()) continue;
         seen.push_back(cc.key);
         const float t = measure(e, 0, 4.f * best_ccm);

@@ -1149,24 +1149,43 @@ hipError_t pack_dispatch(int nbeam, Op& op) {
 }
 
 // Whether a launch over `cells` (sub-interval, channel) cells of L samples takes
-// the packed engine. Its tiles are as wide or wider on fewer waves, so they have
-// to fill the chip (whole blocks -> packed, us):
-//   32..72 beams (16 k to 16 k + 8): 128 tiles, from 48 beams on 96. 36 beams x
-//     1024 channels x 1024 samples, 16 sub-intervals (256 tiles) 194 -> 124, 4
-//     sub-intervals (64) 69 -> 76; 72 beams 4 sub-intervals (128) 353 -> 220, 3 (96)
-//     272 -> 217, one of 340 samples (32) 64 -> 71.
-//   16..19 beams, where only the epilogues are overlapped (two workgroups per
-//     CU): 768 tiles. 19 beams x 4096 channels x 512 samples x 16 (1024) 161 ->
-//     135, 1024 x 1024 x 60 (960) 277 -> 254, 2000 x 1500 x 10 (320) 153 -> 190;
-//     and sub-intervals up to 8192 samples: 20345 (640 tiles) 2950 -> 3310, the
-//     neighbouring workgroups that share 128-byte lines drift apart.
-bool takes_pack(int nbeam, const CcmTune* t, int64_t cells, int L) {
+// the packed engine. Its tiles are as wide or wider on fewer waves, so they have to
+// fill the chip (whole blocks -> packed, us):
+//   32..72 beams (16 k to 16 k + 8): tiles of twice the channels, 128 of them (from 48
+//     beams on 96), and up to 1024 samples, where a round (256 tiles) is mostly
+//     epilogue, fewer rounds than whole blocks need: 48 beams x 1000 channels, 161
+//     samples x 8 (256 tiles, whole blocks 504) 97 -> 36; 35 x 2048, 697 x 4 (128,
+//     256) 51 -> 64; 48 x 4096, 482 x 1 (128, 256) 48 -> 54.
+//   68..72 beams, whose packed step and epilogue cost more (operands in scratch, two
+//     accumulators more per channel pair): rounds x (chunks + 11) 5 / 4 against
+//     rounds x (chunks + 5), up to 4096 samples. 72 beams: 1000 x 300 x 9 (288
+//     tiles, 567) 202 -> 272, 2000 x 87 x 21 549 -> 662, 2048 x 340 x 19 961 -> 832,
+//     1024 x 2048 x 4 309 -> 443, x 8000 x 4 1074 -> 922.
+//   16..19 beams, where only the epilogues are overlapped (two workgroups per CU):
+//     768 tiles of up to 1024 samples, 1536 of up to 4096. 19 beams x 4096 channels:
+//     512 samples x 13 (832) 151 -> 134, 1024 x 13 248 -> 235, 2048 x 13 424 -> 434,
+//     x 25 800 -> 768, x 99 3150 -> 3035, 4096 x 25 1502 -> 1487, 8192 x 24 2750 ->
+//     2799, 20345 x 10 2950 -> 3310: the neighbouring workgroups that share
+//     128-byte lines drift apart. Lined-up beams (ccm_lined_up) queue on the same
+//     memory channels however the epilogues lie: up to 512 samples there (x 13 147
+//     -> 138, 1024 x 13 246 -> 256, 2048 x 13 456 -> 494).
+bool takes_pack(int nbeam, const CcmTune* t, int64_t cells, int L, bool lined) {
   if (t && (t->tile || t->stages || t->engine == 1)) return false;   // a choice of the other
   const int nbf = nbeam / 16, left = nbeam % 16;
   if (nbf < 1 || nbf > 4 || left > (nbf == 1 ? 3 : 8)) return false;
   if (t && t->engine == 2) return true;
-  if (nbf == 1) return cells >= 768 * 64 && L <= 8192;
-  return cells >= (nbf == 2 ? 128 * 64 : 96 * 32);
+  if (nbf == 1) {
+    if (lined) return cells >= 768 * 64 && L <= 512;
+    return cells >= (L <= 1024 ? 768 : 1536) * 64 && L <= 4096;
+  }
+  if (cells < (nbf == 2 ? 128 * 64 : 96 * 32)) return false;
+  const int64_t per = 256 * (nbf == 2 ? 64 : 32);       // cells of a packed round
+  const int64_t most = cells < (int64_t)1 << 40 ? cells : (int64_t)1 << 40;
+  const int64_t packed = (most + per - 1) / per, whole = (2 * most + per - 1) / per;
+  const int nchunk = (L + TC - 1) / TC;
+  if (nbf == 4 && left >= 4)
+    return L > 4096 || packed * 5 * (nchunk + 11) < whole * 4 * (nchunk + 5);
+  return L > 1024 || packed < whole;
 }
 
 // The MFMA engine's instance for a beam count: 16-row blocks NB (including
@@ -1328,13 +1347,21 @@ int ccm_tile_variants(int nbeam) {
   return nb == 2 ? 3 : (nb >= 1 && nb <= 5 ? 1 : 0);
 }
 
+bool ccm_lined_up(const uint8_t* const* beam, int nbeam, int64_t row_stride) {
+  if (row_stride % 1024) return false;
+  for (int b = 1; b < nbeam; ++b)
+    if (((uintptr_t)beam[b] ^ (uintptr_t)beam[0]) & 4095) return false;
+  return true;
+}
+
 hipError_t launch_ccm_mfma(const BeamPtrs& bp, int nbeam, int nchan, int64_t row_stride,
                            int64_t t0, int L, int nsub, int32_t* sum_x, int32_t* sum_xy,
                            int32_t* count, int accumulate, int shared_cu, hipStream_t s,
                            const CcmTune* t, int layout, int64_t kstride, int ksplit, int Llast) {
   LaunchOne op{bp, nbeam, nchan, row_stride, t0, L, nsub, sum_x, sum_xy, count, accumulate,
                t ? t->group_bytes : 0, layout, kstride, ksplit, Llast, s};
-  const bool pack = !shared_cu && takes_pack(nbeam, t, (int64_t)nsub * nchan, L);
+  const bool pack = !shared_cu && takes_pack(nbeam, t, (int64_t)nsub * nchan, L,
+                                             ccm_lined_up(bp.p, nbeam, row_stride));
   return ccm_dispatch(nbeam, shared_cu, pack, op, t);
 }
 
@@ -1346,9 +1373,9 @@ hipError_t launch_ccm_mfma(const BeamPtrs& bp, int nbeam, int nchan, int64_t row
                          accumulate, shared_cu, s, t, layout, kstride, ksplit, L);
 }
 
-hipError_t ccm_class(int nbeam, CcmClass* c, const CcmTune* t, int64_t cells, int L) {
+hipError_t ccm_class(int nbeam, CcmClass* c, const CcmTune* t, int64_t cells, int L, bool lined) {
   Describe op{nbeam, c};
-  const bool pack = takes_pack(nbeam, t, cells, L);
+  const bool pack = takes_pack(nbeam, t, cells, L, lined);
   c->engine = pack ? 2 : 1;
   hipError_t e = ccm_dispatch(nbeam, 0, pack, op, t);
   // the tile group size is a launch argument: part of the class

@@ -35,28 +35,30 @@ int max_split(int nsub, int nchan) {
   return need > (int)want ? need : (int)want;
 }
 
-// Chunks per sub-interval: the least cost, in 32-sample steps of a slot, of
-// rounds x (steps per chunk + a workgroup's prologue and epilogue) and of the
-// records, written by the sums and read by the widening pass (8 bytes a row
-// against the 256 slots x 32 samples x nbeam bytes of a step's channels). The
+// Chunks per sub-interval: the least cost, in quarters of a 32-sample step of a
+// slot, of rounds x (steps per chunk + a workgroup's prologue and epilogue) and of
+// the records, written by the sums and read by the widening pass (8 bytes a row
+// against the 256 slots x 32 samples x nbeam bytes of a step's channels). A packed
+// tile's step, of twice the channels or beside a second workgroup, takes 1.5 or 2
+// of a whole-block one's (36 beams, rounds of 250 steps: 989 against 643 us). The
 // streaming bound is reached by full rounds, not by many workgroups: 19 beams x
 // 4096 channels, 3 sub-intervals of 40690 samples (192 tiles): 11 chunks (2112
 // workgroups, 8.25 rounds) and a launch for the remainder 1971 us with a widening
 // pass of 42 us, 4 chunks (3 rounds) 1826 and 17 us.
-int split_for(int L, int nsub, int nchan, int nbeam, const CcmTune* t) {
+int split_for(int L, int nsub, int nchan, int nbeam, const CcmTune* t, bool lined) {
   const int need = (L + RFI_MAX_COUNT - 1) / RFI_MAX_COUNT;
   const int most = max_split(nsub, nchan) < L / 256 ? max_split(nsub, nchan) : L / 256;
-  CcmClass cc;
-  if (ccm_class(nbeam, &cc, t, (int64_t)nsub * nchan * most, RFI_MAX_COUNT) != hipSuccess)
-    return need;
-  const int64_t ntiles = (int64_t)nsub * ((nchan + cc.cw - 1) / cc.cw);
   const int rows = 1 + (nbeam + 1) / 2;       // record rows per beam
   int best = need;
   int64_t best_cost = INT64_MAX;
   for (int p = need; p <= most || p == need; ++p) {
-    const int64_t steps = ((L + p - 1) / p + 31) / 32;
-    const int64_t cost = (ntiles * p + cc.slots - 1) / cc.slots * (steps + 8) +
-                         ntiles * p * rows / 1024;
+    const int c = (L + p - 1) / p;
+    CcmClass cc;                              // of this launch
+    if (ccm_class(nbeam, &cc, t, (int64_t)nsub * p * nchan, c, lined) != hipSuccess) return need;
+    const int64_t tiles = (int64_t)nsub * p * ((nchan + cc.cw - 1) / cc.cw);
+    const int step = cc.engine != 2 ? 4 : nbeam < 32 ? 8 : 6;
+    const int64_t cost =
+        (tiles + cc.slots - 1) / cc.slots * ((c + 31) / 32 + 8) * step + tiles * rows / 256;
     if (cost < best_cost) {
       best_cost = cost;
       best = p;
@@ -101,7 +103,7 @@ hipError_t launch_ccm_long(const BeamPtrs& bp, int nbeam, int nchan, int64_t row
                            hipStream_t s, const CcmTune* t, int accumulate) {
   if (nsub == 0) return hipSuccess;
   const int nrow = nbeam + npair_of(nbeam);
-  const int P = split_for(L, nsub, nchan, nbeam, t);
+  const int P = split_for(L, nsub, nchan, nbeam, t, ccm_lined_up(bp.p, nbeam, row_stride));
   // whole 32-sample steps per chunk where the last one still has samples
   int c = (L + P - 1) / P;
   const int c32 = (c + 31) / 32 * 32;

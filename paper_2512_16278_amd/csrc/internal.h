@@ -45,8 +45,12 @@ struct CcmClass {
   int engine;
   int epilogue;        // chunks that the epilogue of a shared tile's workgroup costs
 };
-// cells, L: of the whole launch (its cells, its longest sub-interval).
-hipError_t ccm_class(int nbeam, CcmClass* c, const CcmTune* t, int64_t cells, int L);
+// cells, L, lined: of the whole launch (its cells, its longest sub-interval, whether
+// its beams are lined up).
+hipError_t ccm_class(int nbeam, CcmClass* c, const CcmTune* t, int64_t cells, int L, bool lined);
+// Whether the same time row of every beam, and so many rows of one beam, start at the
+// same address modulo 4 KB: their reads then meet on the same memory channels.
+bool ccm_lined_up(const uint8_t* const* beam, int nbeam, int64_t row_stride);
 // Batched sums launch over the items of one class (items in device memory,
 // sorted by wg0); nbeam_of_class is any member's beam count, t its choices;
 // parts: some item has more than one workgroup per tile.

@@ -1,4 +1,6 @@
-"""Helpers for the GPU parity tests: device buffers and oracle-side reshaping."""
+"""Helpers for the GPU parity tests: device buffers, oracle-side reshaping, and which of the sums
+engine's kernels a launch takes."""
+import ctypes
 import sys
 
 import numpy as np
@@ -48,3 +50,22 @@ def eig_buffers(nbeam, ncell, dev, with_vectors=True):
     ev = torch.full((nbeam, ncell), -9.0, dtype=torch.float32, device=dev) if with_vectors else None
     v1 = torch.full((nbeam, ncell), -9.0, dtype=torch.float32, device=dev) if with_vectors else None
     return stat, status, ev, v1
+
+
+class CcmClass(ctypes.Structure):
+    """rfi::CcmClass of csrc/internal.h."""
+    _fields_ = [("key", ctypes.c_longlong), ("cw", ctypes.c_int), ("nh", ctypes.c_int),
+                ("group_bytes", ctypes.c_int), ("slots", ctypes.c_int), ("engine", ctypes.c_int),
+                ("epilogue", ctypes.c_int)]
+
+
+def sums_class(nbeam, cells, L, lined=False):
+    """The sums engine's class for a launch: engine 1 = whole blocks of beams, 2 = packed."""
+    from paper_2512_16278_amd import rfi
+    f = rfi.lib()._ZN3rfi9ccm_classEiPNS_8CcmClassEPKNS_7CcmTuneElib
+    f.argtypes = [ctypes.c_int, ctypes.POINTER(CcmClass), ctypes.c_void_p, ctypes.c_int64,
+                  ctypes.c_int, ctypes.c_bool]
+    f.restype = ctypes.c_int
+    c = CcmClass()
+    assert f(nbeam, ctypes.byref(c), None, cells, L, lined) == 0
+    return c

@@ -309,3 +309,49 @@ def test_batch_accepts_long_sub_intervals():
     items[0].L, items[0].nsub = rfi.RFI_MAX_COUNT_LONG + 1, 1
     assert L.rfi_batch_workspace_size(1, items, C.byref(p)) == 0
     assert L.rfi_last_error()
+
+
+@pytest.mark.parametrize("nbeam,cells,L,lined,packed", [
+    (15, 1 << 30, 100, False, False), (20, 1 << 30, 100, False, False),
+    (41, 1 << 30, 100, False, False), (73, 1 << 30, 100, False, False),
+    # 16..19 beams: 768 tiles of 64 channels up to 1024 samples, 1536 up to 4096
+    (16, 768 * 64, 1024, False, True), (19, 768 * 64 - 1, 1024, False, False),
+    (19, 768 * 64, 1025, False, False), (19, 1536 * 64, 4096, False, True),
+    (19, 1 << 30, 4097, False, False), (19, 99 * 4096, 2048, False, True),
+    (19, 99 * 4096, 2048, True, False), (17, 768 * 64, 512, True, True),
+    (17, 1 << 30, 513, True, False),
+    # fewer rounds than whole blocks, or sub-intervals past 1024 samples
+    (36, 128 * 64, 1024, False, False), (36, 128 * 64 + 1, 1024, False, True),
+    (36, 128 * 64, 1025, False, True), (36, 128 * 64 - 1, 20000, False, False),
+    (48, 128 * 32, 700, False, False), (56, 128 * 32 + 1, 700, False, True),
+    (64, 96 * 32, 1025, False, True), (67, 96 * 32 - 1, 8000, False, False),
+    # 68..72 beams: rounds weighed by chunks
+    (72, 9 * 1000, 300, False, False), (72, 21 * 2000, 87, False, False),
+    (72, 19 * 2048, 340, False, True), (68, 4 * 1024, 2048, False, False),
+    (68, 4 * 1024, 4097, False, True), (71, 40 * 1024, 512, False, True)])
+def test_sums_engine_rule(nbeam, cells, L, lined, packed):
+    """Which engine a sums launch takes, on both sides of every line of the rule; a tune entry's
+    tile or ring depth keeps the whole blocks it was measured on."""
+    _lib("librfi.so")
+    from gpu_util import sums_class
+    assert sums_class(nbeam, cells, L, lined).engine == (2 if packed else 1)
+
+
+def test_lined_up_beams():
+    """Beams count as lined up when all start at one address modulo 4 KB and the row stride is a
+    multiple of 1 KB; the library's own placement never is."""
+    L = _lib("librfi.so")
+    from paper_2512_16278_amd import rfi
+    f = L._ZN3rfi12ccm_lined_upEPKPKhil
+    f.argtypes = [C.c_void_p, C.c_int, C.c_int64]
+    f.restype = C.c_bool
+
+    def lined(addr, stride):
+        return f((C.c_void_p * len(addr))(*addr), len(addr), stride)
+
+    one = [4096 * (3 + 5 * b) + 512 for b in range(19)]
+    assert lined(one, 4096) and lined(one, 1024) and lined(one[:1], 2048)
+    assert not lined(one, 1040) and not lined(one, 512)
+    assert not lined(one[:-1] + [one[-1] + 16], 4096)
+    offs, _ = rfi.rfi_beam_offsets(19, 1000, 4096)
+    assert not lined([1 << 20 | o for o in offs], 4096)

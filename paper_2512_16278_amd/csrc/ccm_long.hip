@@ -44,27 +44,38 @@ int max_split(int nsub, int nchan) {
 // streaming bound is reached by full rounds, not by many workgroups: 19 beams x
 // 4096 channels, 3 sub-intervals of 40690 samples (192 tiles): 11 chunks (2112
 // workgroups, 8.25 rounds) and a launch for the remainder 1971 us with a widening
-// pass of 42 us, 4 chunks (3 rounds) 1826 and 17 us.
+// pass of 42 us, 4 chunks (3 rounds) 1826 and 17 us. Where several workgroups share
+// a CU (up to 7 beams) one round, which all start and end together, is up to a tenth
+// slower than its steps say, so four rounds or more are taken at up to a fifth of
+// additional cost: 1 sub-interval of 100000 samples x 4096 channels in 8 and 32
+// chunks: 2 beams 327 and 288 us, 4 beams 358 and 339, 6 beams 529 and 470.
 int split_for(int L, int nsub, int nchan, int nbeam, const CcmTune* t, bool lined) {
   const int need = (L + RFI_MAX_COUNT - 1) / RFI_MAX_COUNT;
   const int most = max_split(nsub, nchan) < L / 256 ? max_split(nsub, nchan) : L / 256;
   const int rows = 1 + (nbeam + 1) / 2;       // record rows per beam
-  int best = need;
-  int64_t best_cost = INT64_MAX;
+  int best = need, many = 0;                  // many: of four rounds or more
+  int64_t best_cost = INT64_MAX, many_cost = INT64_MAX;
+  bool one_round = false;
   for (int p = need; p <= most || p == need; ++p) {
     const int c = (L + p - 1) / p;
     CcmClass cc;                              // of this launch
     if (ccm_class(nbeam, &cc, t, (int64_t)nsub * p * nchan, c, lined) != hipSuccess) return need;
     const int64_t tiles = (int64_t)nsub * p * ((nchan + cc.cw - 1) / cc.cw);
     const int step = cc.engine != 2 ? 4 : nbeam < 32 ? 8 : 6;
-    const int64_t cost =
-        (tiles + cc.slots - 1) / cc.slots * ((c + 31) / 32 + 8) * step + tiles * rows / 256;
+    const int64_t rounds = (tiles + cc.slots - 1) / cc.slots;
+    const int64_t cost = rounds * ((c + 31) / 32 + 8) * step + tiles * rows / 256;
+    const bool shared_cu = cc.engine == 1 && cc.slots > 256;
     if (cost < best_cost) {
       best_cost = cost;
       best = p;
+      one_round = shared_cu && rounds == 1;
+    }
+    if (shared_cu && tiles >= 4 * cc.slots && cost < many_cost) {
+      many_cost = cost;
+      many = p;
     }
   }
-  return best;
+  return one_round && many && many_cost <= best_cost + best_cost / 5 ? many : best;
 }
 
 // rec64[cell][row] = sum over the P chunk records of that cell; count[k] = L.

@@ -40,6 +40,10 @@ namespace rfi {
 namespace {
 
 constexpr int kRowCells = kTriCellPad;   // cells per workgroup
+// Launches of at most this many cells take one wavefront (four cells) per workgroup
+// instead, to reach more CUs' LDS and load paths: 20 beams, 1024 cells 26 -> 21 us, 40
+// beams 57 -> 49, 2048 cells 57 -> 52, 4096 57 -> 58.
+constexpr int64_t kRowFew = 2048;
 constexpr int kRowThreads = 256;
 constexpr int kVecs = 8;           // doubles of LDS per row index and cell
 
@@ -50,7 +54,8 @@ __device__ __forceinline__ int64_t xcd_order_row(int64_t b, int64_t total) {
 
 // S, E: rows per lane and leading rows as above; N: columns held (<= 16 S + E).
 // W: int64 cell records; NC: the non-centred matrix (see eig_tri.hip). cell0:
-// first cell of each item, every item's range padded to kRowCells.
+// first cell of each item, every item's range padded to kRowCells. A workgroup has
+// 16 lanes to a cell.
 template <int S, int E, int N, bool W, bool NC>
 __global__ __launch_bounds__(kRowThreads, (S == 1 ? 3 : 2)) void eig_row_kernel(
     EigArgs g, const EigArgs* items, const int64_t* cell0, int nitem, const double* zb) {
@@ -58,7 +63,8 @@ __global__ __launch_bounds__(kRowThreads, (S == 1 ? 3 : 2)) void eig_row_kernel(
   using ST = std::conditional_t<W, int64_t, int32_t>;
   typedef const __attribute__((address_space(1))) ST gst;
   extern __shared__ __attribute__((aligned(16))) double lds[];
-  int64_t c0 = xcd_order_row(blockIdx.x, gridDim.x) * kRowCells;
+  const int nthr = blockDim.x, ncl = nthr >> 4;        // threads, cells of a workgroup
+  int64_t c0 = xcd_order_row(blockIdx.x, gridDim.x) * ncl;
   if (items) {
     int lo = 0, hi = nitem - 1;
     while (lo < hi) {
@@ -70,7 +76,8 @@ __global__ __launch_bounds__(kRowThreads, (S == 1 ? 3 : 2)) void eig_row_kernel(
   }
   const int n = g.nbeam, np = n * (n + 1) / 2, nrow = n + np;
   const int64_t ncell = (int64_t)g.nsub * g.nchan;
-  const int valid = ncell - c0 < kRowCells ? (int)(ncell - c0) : kRowCells;
+  if (c0 >= ncell) return;                             // padding of an item's range
+  const int valid = ncell - c0 < ncl ? (int)(ncell - c0) : ncl;
   // stage the sums of the workgroup's cells, [cell][row]
   ST* const st = (ST*)lds;
   if (W || g.layout) {
@@ -86,37 +93,37 @@ __global__ __launch_bounds__(kRowThreads, (S == 1 ? 3 : 2)) void eig_row_kernel(
     constexpr int kQuads = kRowCells * (N + N * (N + 1) / 2) * (int)(sizeof(ST) / 4) / 4;
     constexpr int kQ = (kQuads + kRowThreads - 1) / kRowThreads;
     constexpr int kB = kQ < 12 ? kQ : 12;
-    for (int q0 = threadIdx.x; q0 < quads; q0 += kRowThreads * kB) {
+    for (int q0 = threadIdx.x; q0 < quads; q0 += nthr * kB) {
       v4 v[kB];
 #pragma unroll
       for (int u = 0; u < kB; ++u) {
-        const int q = q0 + u * kRowThreads;
+        const int q = q0 + u * nthr;
         v[u] = src[q < quads ? q : quads - 1];
       }
 #pragma unroll
       for (int u = 0; u < kB; ++u)
-        if (q0 + u * kRowThreads < quads) ((v4*)st)[q0 + u * kRowThreads] = v[u];
+        if (q0 + u * nthr < quads) ((v4*)st)[q0 + u * nthr] = v[u];
     }
     // the rest: a last workgroup may end inside 16 bytes
-    for (int q = 4 * quads + threadIdx.x; q < words; q += kRowThreads)
+    for (int q = 4 * quads + threadIdx.x; q < words; q += nthr)
       ((int*)st)[q] = ((const __attribute__((address_space(1))) int*)src)[q];
   } else {
     // rows layout: 16 consecutive cells of a row per 16 threads
     constexpr int kLd = 16;
-    const int c = threadIdx.x & 15;
+    const int c = threadIdx.x & (ncl - 1);
     const int64_t cell = c0 + (c < valid ? c : valid - 1);
-    for (int q0 = threadIdx.x >> 4; q0 < nrow; q0 += kRowThreads / 16 * kLd) {
+    for (int q0 = threadIdx.x / ncl; q0 < nrow; q0 += 16 * kLd) {
       ST v[kLd];
 #pragma unroll
       for (int u = 0; u < kLd; ++u) {
-        int q = q0 + u * (kRowThreads / 16);
+        int q = q0 + u * 16;
         q = q < nrow ? q : nrow - 1;
         v[u] = *((gst*)(q < n ? g.sum_x + (int64_t)q * ncell
                               : g.sum_xy + (int64_t)(q - n) * ncell) + cell);
       }
 #pragma unroll
       for (int u = 0; u < kLd; ++u) {
-        const int q = q0 + u * (kRowThreads / 16);
+        const int q = q0 + u * 16;
         if (q < nrow) st[c * nrow + q] = v[u];
       }
     }
@@ -180,6 +187,12 @@ __global__ __launch_bounds__(kRowThreads, (S == 1 ? 3 : 2)) void eig_row_kernel(
   double offsq = 0.0, dgsq = 0.0;
   static_for<0, N>([&](auto J_) {
     constexpr int j = RFI_CI(J_);
+    if constexpr (NC && j >= 2)
+      if (j >= n) {                                    // no divisions for padding columns
+        static_for<0, S>([&](auto A_) { A[RFI_CI(A_)][j] = 0.0; });
+        if constexpr (j < E) B[j] = 0.0;
+        return;
+      }
     double Sj, dj;
     if constexpr (j < E) {
       Sj = bcast<j & 15>(Se);
@@ -434,15 +447,16 @@ __global__ __launch_bounds__(kRowThreads, (S == 1 ? 3 : 2)) void eig_row_kernel(
 template <int S, int E, int N, bool W, bool NC>
 hipError_t launch_row(const EigArgs& a, const EigArgs* items, const int64_t* cell0, int nitem,
                       int64_t total, const double* zb, hipStream_t s) {
-  const size_t stage = (size_t)kRowCells * (N + N * (N + 1) / 2) * (W ? 8 : 4);
-  const size_t tri = (size_t)kRowCells * (kVecs * N + 2) * 8;
+  const int ncl = total <= kRowFew ? 4 : kRowCells;
+  const size_t stage = (size_t)ncl * (N + N * (N + 1) / 2) * (W ? 8 : 4);
+  const size_t tri = (size_t)ncl * (kVecs * N + 2) * 8;
   const size_t shm = stage > tri ? stage : tri;
   const auto kern = eig_row_kernel<S, E, N, W, NC>;
   hipError_t e = hipFuncSetAttribute((const void*)kern,
                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)shm);
   if (e != hipSuccess) return e;
-  const int64_t wg = (total + kRowCells - 1) / kRowCells;
-  hipLaunchKernelGGL(kern, dim3((unsigned)wg), dim3(kRowThreads), shm, s, a, items, cell0, nitem,
+  const int64_t wg = (total + ncl - 1) / ncl;
+  hipLaunchKernelGGL(kern, dim3((unsigned)wg), dim3(ncl * 16), shm, s, a, items, cell0, nitem,
                      zb);
   return hipGetLastError();
 }

@@ -357,7 +357,8 @@ __device__ __forceinline__ Spectrum spectrum_bounds(const double2* ae, const dou
   ghi = group_max<W>(ghi);
   lb = group_max<W>(lb);
   const double span = fmax(ghi - glo, 1e-300);
-  return {glo - 1e-12 * span, ghi + 1e-12 * span, lb - 1e-12 * span};
+  // (two rows: the block is the matrix)
+  return {glo - 1e-12 * span, (n == 2 ? lb : ghi) + 1e-12 * span, lb - 1e-12 * span};
 }
 
 // The largest eigenvalue, to 2e-14 of max(|lambda_1|, floor) (the order of the

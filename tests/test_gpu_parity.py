@@ -613,6 +613,50 @@ def test_flag_one_launch(dev, n):
         assert np.array_equal(mask, ref.mask) and st["iterations"] == ref.iterations, i
 
 
+@pytest.mark.parametrize("nbeam", [2, 3, 16, 20, 24, 36, 40])
+def test_eig_tridiag_few_cells(dev, nbeam):
+    """Launches on both sides of the cell count up to which a workgroup has four cells instead of
+    16, with ragged last workgroups: the same bits for every cell, correlation and raw moments,
+    rows and (whole-block call in one group and in several) cell records."""
+    import torch
+    from paper_2512_16278_amd import rfi
+    rng = np.random.default_rng(70 + nbeam)
+    nsub, nc, L = 2, 1037, 48
+    x = rng.integers(0, 256, size=(nbeam, nsub * L, nc), dtype=np.uint8)
+    _, _, _, (buf, blk, sx, sxy, cnt) = run_ccm(x, L, nsub, dev, 1)
+
+    def eig(k0, k1, nc_raw):
+        cells = slice(k0 * nc, k1 * nc)
+        stat, st8, ev, v1 = eig_buffers(nbeam, (k1 - k0) * nc, dev)
+        a, b, c = sx[:, cells].contiguous(), sxy[:, cells].contiguous(), cnt[k0:k1].contiguous()
+        say("eig few cells", nbeam, k0, k1, nc_raw)
+        if nc_raw:
+            rfi.rfi_eig_noncentred(nbeam, k1 - k0, nc, a, b, c, None, stat, st8, eigvals=ev, v1=v1)
+        else:
+            rfi.rfi_eig_batched(nbeam, k1 - k0, nc, a, b, c, stat, st8, eigvals=ev, v1=v1,
+                                solver=rfi.RFI_EIG_TRIDIAG)
+        torch.cuda.synchronize()
+        return [t.cpu().numpy() for t in (stat, st8, ev, v1)]
+
+    for nc_raw in (False, True):
+        both = eig(0, 2, nc_raw)
+        for u, v, w in zip(both, eig(0, 1, nc_raw), eig(1, 2, nc_raw)):
+            assert np.array_equal(u, np.concatenate([v, w], axis=-1)), nc_raw
+    if nbeam <= 20:
+        return                              # the whole-block call takes the per-lane solver
+    got = []
+    for group in (0, 1):
+        p = rfi.process_params(L, nsub, group=group)
+        ws = torch.empty(rfi.rfi_process_workspace_size(nbeam, nc, p), dtype=torch.uint8, device=dev)
+        stat, st8, ev, v1 = eig_buffers(nbeam, nsub * nc, dev)
+        mask = torch.empty(nsub * nc, dtype=torch.uint8, device=dev)
+        rfi.rfi_process_block(blk, p, stat, st8, mask, ws, eigvals=ev, v1=v1)
+        torch.cuda.synchronize()
+        got.append([t.cpu().numpy() for t in (stat, st8, ev, v1, mask)])
+    for u, v in zip(*got):
+        assert np.array_equal(u, v)
+
+
 @pytest.mark.parametrize("n", [12287, 12288, 12289])
 def test_flag_largest_one_launch(dev, n):
     """Around the largest block that is clipped in a single launch."""

@@ -1052,17 +1052,17 @@ __global__ __launch_bounds__(256) void zero_items_kernel(const CcmItem* items) {
 // nbeam + npair rows cost at one per ns and CU (72 beams 34: 4096 channels x 700
 // samples, 128 tiles, in 2 parts 196 us, whole 143 us). 19 beams: 16 tiles of
 // 1024 samples in 8 parts 49 -> 20 us (and 3 us to zero).
-struct Share {
-  int nwhole, parts;
-};
 template <class C>
 int shared_epilogue(int nbeam) {
   return C::DIRECT ? 6 + (nbeam + 3) * 3 / 8 : 12;
 }
-Share ccm_share(int64_t ntiles, int L, int slots, int epilogue) {
+
+}  // namespace
+
+CcmShare ccm_share(int64_t ntiles, int L, int slots, int epilogue) {
   const int nchunk = (L + TC - 1) / TC;
   const int64_t full = ntiles / slots, tail = ntiles - full * slots;
-  Share sh{(int)ntiles, 1};
+  CcmShare sh{(int)ntiles, 1};
   if (tail == 0 || nchunk < 8) return sh;
   int64_t best = (full + 1) * (nchunk + 8) * 49 / 50;
   for (int p = 2; p <= 32 && p * 4 <= nchunk; ++p) {
@@ -1070,11 +1070,13 @@ Share ccm_share(int64_t ntiles, int L, int slots, int epilogue) {
                          (tail * p + slots - 1) / slots * ((nchunk + p - 1) / p + epilogue) + 4;
     if (cost < best) {
       best = cost;
-      sh = Share{(int)(full * slots), p};
+      sh = CcmShare{(int)(full * slots), p};
     }
   }
   return sh;
 }
+
+namespace {
 
 template <class C, class K>
 hipError_t launch_cfg(K kern, int nh, const BeamPtrs& bp, int nbeam, int nchan, int64_t row_stride,
@@ -1088,7 +1090,8 @@ hipError_t launch_cfg(K kern, int nh, const BeamPtrs& bp, int nbeam, int nchan, 
   if (e != hipSuccess) return e;
   const int64_t ntiles = (int64_t)nsub * nct;
   const int G = group_tiles(C::WIDTH, group_bytes);
-  const Share sh = ksplit > 1 ? Share{(int)ntiles, 1} : ccm_share(ntiles, L, C::SLOTS, shared_epilogue<C>(nbeam));
+  const CcmShare sh = ksplit > 1 ? CcmShare{(int)ntiles, 1}
+                                 : ccm_share(ntiles, L, C::SLOTS, shared_epilogue<C>(nbeam));
   if (sh.parts > 1 && !accumulate) {
     e = launch_zero(sum_x, sum_xy, nbeam, (int64_t)nsub * nchan,
                     (int64_t)(sh.nwhole / nct) * nchan, layout, s);

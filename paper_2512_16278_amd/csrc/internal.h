@@ -51,6 +51,12 @@ hipError_t ccm_class(int nbeam, CcmClass* c, const CcmTune* t, int64_t cells, in
 // Whether the same time row of every beam, and so many rows of one beam, start at the
 // same address modulo 4 KB: their reads then meet on the same memory channels.
 bool ccm_lined_up(const uint8_t* const* beam, int nbeam, int64_t row_stride);
+// The tiles of a launch that go to one workgroup each; the samples of the rest are
+// shared out to `parts` workgroups.
+struct CcmShare {
+  int nwhole, parts;
+};
+CcmShare ccm_share(int64_t ntiles, int L, int slots, int epilogue);
 // Batched sums launch over the items of one class (items in device memory,
 // sorted by wg0); nbeam_of_class is any member's beam count, t its choices;
 // parts: some item has more than one workgroup per tile.

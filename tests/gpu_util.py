@@ -69,3 +69,14 @@ def sums_class(nbeam, cells, L, lined=False):
     c = CcmClass()
     assert f(nbeam, ctypes.byref(c), None, cells, L, lined) == 0
     return c
+
+
+def sums_parts(nbeam, nchan, nsub, L):
+    """(tiles that go to one workgroup each, workgroups per tile of the rest) of a sums launch."""
+    from paper_2512_16278_amd import rfi
+    c = sums_class(nbeam, nsub * nchan, L)
+    f = rfi.lib()._ZN3rfi9ccm_shareEliii
+    f.argtypes = [ctypes.c_int64, ctypes.c_int, ctypes.c_int, ctypes.c_int]
+    f.restype = ctypes.c_int64                # {int nwhole, parts}
+    r = f(nsub * -(-nchan // c.cw), L, c.slots, c.epilogue) & (2 ** 64 - 1)
+    return r & 0xffffffff, r >> 32

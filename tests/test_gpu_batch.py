@@ -212,6 +212,59 @@ def test_batch_graph_replays(dev):
     g.close()
 
 
+# items whose classes take the packed sums engine, several beam counts to an instance and one long
+# item in each, which is cut in time (nbeam, nchan, L, nsub, t0)
+PACKED = [(19, 1024, 40, 30, 0), (17, 1000, 33, 20, 2), (16, 64, 1000, 1, 0),
+          (36, 500, 64, 11, 0), (39, 333, 50, 12, 1), (37, 64, 3000, 1, 0),
+          (68, 200, 90, 12, 0), (71, 100, 70, 30, 5), (70, 40, 900, 2, 0),
+          (72, 300, 210, 15, 0), (72, 40, 1000, 1, 3)]
+
+
+def test_batch_packed_classes(dev):
+    """Classes large enough for the packed sums engine: every block as the whole-block call gives
+    it alone, bit for bit, eager and in a graph replayed with eager work in between."""
+    import torch
+    from gpu_util import sums_class
+    from paper_2512_16278_amd import rfi
+    classes = {}
+    for shape in PACKED:
+        classes.setdefault(sums_class(shape[0], 1 << 40, 900).key, []).append(shape)
+    assert sorted(len(v) for v in classes.values()) == [2, 3, 3, 3]
+    for of in classes.values():
+        cells, longest = sum(s[1] * s[3] for s in of), max(s[2] for s in of)
+        assert all(sums_class(s[0], cells, longest).engine == 2 for s in of)
+    blocks = []
+    for i, (nb, nc, L, nsub, t0) in enumerate(PACKED):
+        buf = upload(_data(nb, nc, t0 + nsub * L, 500 + i), dev)
+        blocks.append(dict(buf=buf, blk=rfi.make_block(buf, nc), nb=nb, nc=nc, L=L, nsub=nsub,
+                           t0=t0, protect_chan=None, state=None))
+    ref = [_single(b, dev) for b in blocks]
+    items = _batch_items(blocks, dev)
+    bt = rfi.Batch(items)
+    ws = torch.empty(bt.workspace_size(), dtype=torch.uint8, device=dev)
+
+    def check(what):
+        torch.cuda.synchronize()
+        for b, it, r in zip(blocks, items, ref):
+            for k, u in zip(("stat", "status", "mask", "out"), r):
+                assert np.array_equal(it[k].cpu().numpy(), u), (what, b["nb"], k)
+            it["stat"].fill_(-3.0)
+            it["mask"].fill_(9)
+
+    say("batch: packed classes")
+    ws.fill_(0x5A)                                      # sums that are not zeroed would show
+    bt.run(ws)
+    check("eager")
+    say("batch: packed classes, graph")
+    g = bt.graph(ws)
+    for rep in range(3):
+        junk = torch.randn(1 << 20, device=dev).sum()
+        g.launch()
+        check(rep)
+        assert float(junk) == float(junk)
+    g.close()
+
+
 def test_batch_empty_and_errors(dev):
     import torch
     from paper_2512_16278_amd import rfi

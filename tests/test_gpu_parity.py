@@ -164,6 +164,75 @@ def test_ccm_packed(dev, nbeam, nchan, nsub, L):
     assert np.array_equal(rec.cpu().numpy(), np.concatenate([rsx, rsxy]).T)
 
 
+@pytest.mark.parametrize("nbeam,nchan,nsub,L", [(69, 2050, 2, 207), (71, 2051, 2, 209)])
+def test_ccm_packed_68_to_71(dev, nbeam, nchan, nsub, L):
+    """As test_ccm_packed for 68..71 beams, which take the packed engine from 6 chunks on; stages
+    that end in the first and the second half of a step."""
+    from gpu_util import sums_class
+    assert sums_class(nbeam, nsub * nchan, L).engine == 2
+    test_ccm_packed(dev, nbeam, nchan, nsub, L)
+
+
+@pytest.mark.parametrize("nbeam,nchan,nsub,L", [
+    (17, 710, 90, 500), (33, 570, 31, 500), (36, 570, 31, 490), (40, 570, 31, 511),
+    (50, 270, 29, 1099), (53, 270, 29, 1100), (56, 270, 29, 1125), (66, 270, 29, 1283),
+    (70, 270, 29, 1340), (72, 270, 29, 1390)])
+def test_ccm_packed_parts(dev, nbeam, nchan, nsub, L):
+    """Packed launches whose last round is shared out in time: whole tiles that end inside a
+    sub-interval's row of tiles, ragged channel tiles and last chunks, sums added with atomics from
+    the staging and (48 beams on) from the accumulators. Rows against FP64 products (exact), then
+    accumulated on top of themselves; cell records of up to 511 samples likewise, longer ones
+    through the whole-block call, whose outputs have to be those of the rows bit for bit."""
+    import torch
+    from gpu_util import sums_class, sums_parts
+    from paper_2512_16278_amd import rfi
+    assert sums_class(nbeam, nsub * nchan, L).engine == 2
+    nwhole, parts = sums_parts(nbeam, nchan, nsub, L)
+    nct = -(-nchan // sums_class(nbeam, nsub * nchan, L).cw)
+    assert parts > 1 and 0 < nwhole < nsub * nct and nwhole % nct
+    g = torch.Generator().manual_seed(nbeam)
+    x = torch.randint(0, 256, (nbeam, nsub * L, nchan), dtype=torch.uint8, generator=g)
+    x[:, : L // 2, ::5] = 255
+    buf = upload(x.numpy(), dev)
+    blk = rfi.make_block(buf, nchan)
+    sx, sxy, cnt = sums_buffers(nbeam, nsub, nchan, dev)
+    say("ccm packed parts", nbeam, nchan, nsub, L, "whole", nwhole, "parts", parts)
+    rfi.rfi_ccm_accumulate(blk, 0, L, nsub, sx, sxy, cnt)
+    torch.cuda.synchronize()
+    iu = torch.triu_indices(nbeam, nbeam)
+    ref = []
+    for k in range(nsub):
+        xk = x[:, k * L: (k + 1) * L].permute(2, 0, 1).to(torch.float64).contiguous()
+        p = torch.bmm(xk, xk.transpose(1, 2).contiguous())
+        ref.append(torch.cat([xk.sum(dim=2), p[:, iu[0], iu[1]]], dim=1).to(torch.int64))
+    ref = torch.cat(ref)                                       # [cell, row]
+    got = torch.cat([sx, sxy]).cpu().to(torch.int64)
+    assert torch.equal(got, ref.T) and (cnt.cpu() == L).all()
+    st1, s81, ev1, v11 = eig_buffers(nbeam, nsub * nchan, dev)
+    rfi.rfi_eig_batched(nbeam, nsub, nchan, sx, sxy, cnt, st1, s81, eigvals=ev1, v1=v11)
+    rfi.rfi_ccm_accumulate(blk, 0, L, nsub, sx, sxy, cnt, accumulate=1)
+    torch.cuda.synchronize()
+    assert torch.equal(torch.cat([sx, sxy]).cpu().to(torch.int64), 2 * ref.T)
+    assert (cnt.cpu() == 2 * L).all()
+    if L < 512:                                                # one chunk of the long route
+        rec = torch.full((nsub * nchan, ref.shape[1]), -7, dtype=torch.int64, device=dev)
+        ws = torch.empty(rfi.rfi_ccm_long_workspace_size(nbeam, nchan, nsub), dtype=torch.uint8,
+                         device=dev)
+        say("ccm packed parts, records")
+        rfi.rfi_ccm_accumulate_long(blk, 0, L, nsub, rec, cnt, ws)
+        torch.cuda.synchronize()
+        assert torch.equal(rec.cpu(), ref)
+    p = rfi.process_params(L, nsub)
+    ws = torch.empty(rfi.rfi_process_workspace_size(nbeam, nchan, p), dtype=torch.uint8, device=dev)
+    st2, s82, ev2, v12 = eig_buffers(nbeam, nsub * nchan, dev)
+    mask = torch.empty(nsub * nchan, dtype=torch.uint8, device=dev)
+    say("ccm packed parts, whole-block call")
+    rfi.rfi_process_block(blk, p, st2, s82, mask, ws, eigvals=ev2, v1=v12)
+    torch.cuda.synchronize()
+    for u, v in ((st1, st2), (s81, s82), (ev1, ev2), (v11, v12)):
+        assert torch.equal(u, v)
+
+
 def test_ccm_accumulate_across_calls(dev):
     import torch
     from paper_2512_16278_amd import rfi

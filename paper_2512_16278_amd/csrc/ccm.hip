@@ -33,6 +33,7 @@
 #include <stdlib.h>
 #include <string.h>
 
+#include <algorithm>
 #include <type_traits>
 
 #include "internal.h"
@@ -1062,15 +1063,15 @@ int shared_epilogue(int nbeam) {
 CcmShare ccm_share(int64_t ntiles, int L, int slots, int epilogue) {
   const int nchunk = (L + TC - 1) / TC;
   const int64_t full = ntiles / slots, tail = ntiles - full * slots;
-  CcmShare sh{(int)ntiles, 1};
+  CcmShare sh{(int)ntiles, 1, (full + (tail > 0)) * (nchunk + 8)};
   if (tail == 0 || nchunk < 8) return sh;
-  int64_t best = (full + 1) * (nchunk + 8) * 49 / 50;
+  int64_t best = sh.cost * 49 / 50;
   for (int p = 2; p <= 32 && p * 4 <= nchunk; ++p) {
     const int64_t cost = full * (nchunk + 8) +
                          (tail * p + slots - 1) / slots * ((nchunk + p - 1) / p + epilogue) + 4;
     if (cost < best) {
       best = cost;
-      sh = CcmShare{(int)(full * slots), p};
+      sh = CcmShare{(int)(full * slots), p, cost};
     }
   }
   return sh;
@@ -1090,7 +1091,7 @@ hipError_t launch_cfg(K kern, int nh, const BeamPtrs& bp, int nbeam, int nchan, 
   if (e != hipSuccess) return e;
   const int64_t ntiles = (int64_t)nsub * nct;
   const int G = group_tiles(C::WIDTH, group_bytes);
-  const CcmShare sh = ksplit > 1 ? CcmShare{(int)ntiles, 1}
+  const CcmShare sh = ksplit > 1 ? CcmShare{(int)ntiles, 1, 0}
                                  : ccm_share(ntiles, L, C::SLOTS, shared_epilogue<C>(nbeam));
   if (sh.parts > 1 && !accumulate) {
     e = launch_zero(sum_x, sum_xy, nbeam, (int64_t)nsub * nchan,
@@ -1165,25 +1166,31 @@ hipError_t pack_dispatch(int nbeam, Op& op) {
 //     tiles, 567) 202 -> 272, 2000 x 87 x 21 549 -> 662, 2048 x 340 x 19 961 -> 832,
 //     1024 x 2048 x 4 309 -> 443, x 8000 x 4 1074 -> 922.
 //   16..19 beams, where only the epilogues are overlapped (two workgroups per CU):
-//     768 tiles of up to 1024 samples, 1536 of up to 4096. 19 beams x 4096 channels:
-//     512 samples x 13 (832) 151 -> 134, 1024 x 13 248 -> 235, 2048 x 13 424 -> 434,
-//     x 25 800 -> 768, x 99 3150 -> 3035, 4096 x 25 1502 -> 1487, 8192 x 24 2750 ->
-//     2799, 20345 x 10 2950 -> 3310: the neighbouring workgroups that share
-//     128-byte lines drift apart. Lined-up beams (ccm_lined_up) queue on the same
-//     memory channels however the epilogues lie: up to 512 samples there (x 13 147
-//     -> 138, 1024 x 13 246 -> 256, 2048 x 13 456 -> 494).
+//     768 tiles of up to 1024 samples; of up to 3072 by the rounds that either needs
+//     (CcmShare::cost): a packed one, of twice the workgroups, takes 2 x (0.875 +
+//     samples / 65536) whole ones. packed / whole, 19 beams x 4096 channels: 832
+//     tiles (3.25 whole rounds, the last one shared out) of 1100 / 1500 / 2000 / 3000
+//     samples 0.96 / 0.99 / 1.02 / 1.02, 960 tiles 0.92 / 0.94 / 0.94 / 0.97, 3200
+//     tiles 0.92 / 0.93 / 0.95 / 0.98; 1536 of 8192 1.02, 640 of 20345 1.12 (the
+//     neighbouring workgroups that share 128-byte lines drift apart). Lined-up beams
+//     (ccm_lined_up) queue on the same memory channels however the epilogues lie: up
+//     to 512 samples there (832 tiles: 512 147 -> 138 us, 1024 246 -> 256, 2048 456
+//     -> 494).
 bool takes_pack(int nbeam, const CcmTune* t, int64_t cells, int L, bool lined) {
   if (t && (t->tile || t->stages || t->engine == 1)) return false;   // a choice of the other
   const int nbf = nbeam / 16, left = nbeam % 16;
   if (nbf < 1 || nbf > 4 || left > (nbf == 1 ? 3 : 8)) return false;
   if (t && t->engine == 2) return true;
   if (nbf == 1) {
-    if (lined) return cells >= 768 * 64 && L <= 512;
-    return cells >= (L <= 1024 ? 768 : 1536) * 64 && L <= 4096;
+    if (cells < 768 * 64 || L > (lined ? 512 : 3072)) return false;
+    if (L <= 1024) return true;
+    const int64_t tiles = std::min<int64_t>(cells, (int64_t)1 << 40) / 64;
+    return ccm_share(tiles, L, 512, 12).cost * 2 * (57344 + L) <
+           ccm_share(tiles, L, 256, 12).cost * 65536;
   }
   if (cells < (nbf == 2 ? 128 * 64 : 96 * 32)) return false;
   const int64_t per = 256 * (nbf == 2 ? 64 : 32);       // cells of a packed round
-  const int64_t most = cells < (int64_t)1 << 40 ? cells : (int64_t)1 << 40;
+  const int64_t most = std::min<int64_t>(cells, (int64_t)1 << 40);
   const int64_t packed = (most + per - 1) / per, whole = (2 * most + per - 1) / per;
   const int nchunk = (L + TC - 1) / TC;
   if (nbf == 4 && left >= 4)

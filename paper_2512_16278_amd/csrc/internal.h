@@ -52,9 +52,10 @@ hipError_t ccm_class(int nbeam, CcmClass* c, const CcmTune* t, int64_t cells, in
 // same address modulo 4 KB: their reads then meet on the same memory channels.
 bool ccm_lined_up(const uint8_t* const* beam, int nbeam, int64_t row_stride);
 // The tiles of a launch that go to one workgroup each; the samples of the rest are
-// shared out to `parts` workgroups.
+// shared out to `parts` workgroups. cost: in 32-sample chunks of a slot.
 struct CcmShare {
   int nwhole, parts;
+  int64_t cost;
 };
 CcmShare ccm_share(int64_t ntiles, int L, int slots, int epilogue);
 // Batched sums launch over the items of one class (items in device memory,

@@ -77,6 +77,6 @@ def sums_parts(nbeam, nchan, nsub, L):
     c = sums_class(nbeam, nsub * nchan, L)
     f = rfi.lib()._ZN3rfi9ccm_shareEliii
     f.argtypes = [ctypes.c_int64, ctypes.c_int, ctypes.c_int, ctypes.c_int]
-    f.restype = ctypes.c_int64                # {int nwhole, parts}
+    f.restype = ctypes.c_int64                # the first eight bytes: {int nwhole, parts; ...}
     r = f(nsub * -(-nchan // c.cw), L, c.slots, c.epilogue) & (2 ** 64 - 1)
     return r & 0xffffffff, r >> 32

@@ -314,10 +314,11 @@ def test_batch_accepts_long_sub_intervals():
 @pytest.mark.parametrize("nbeam,cells,L,lined,packed", [
     (15, 1 << 30, 100, False, False), (20, 1 << 30, 100, False, False),
     (41, 1 << 30, 100, False, False), (73, 1 << 30, 100, False, False),
-    # 16..19 beams: 768 tiles of 64 channels up to 1024 samples, 1536 up to 4096
+    # 16..19 beams: 768 tiles of 64 channels up to 1024 samples, by rounds up to 3072
+    (19, 832 * 64, 2048, False, False), (19, 960 * 64, 2048, False, True),
     (16, 768 * 64, 1024, False, True), (19, 768 * 64 - 1, 1024, False, False),
-    (19, 768 * 64, 1025, False, False), (19, 1536 * 64, 4096, False, True),
-    (19, 1 << 30, 4097, False, False), (19, 99 * 4096, 2048, False, True),
+    (19, 768 * 64, 1025, False, False), (19, 1536 * 64, 3072, False, True),
+    (19, 1 << 30, 3073, False, False), (19, 99 * 4096, 2048, False, True),
     (19, 99 * 4096, 2048, True, False), (17, 768 * 64, 512, True, True),
     (17, 1 << 30, 513, True, False),
     # fewer rounds than whole blocks, or sub-intervals past 1024 samples

@@ -614,12 +614,16 @@ rfi_status rfi_tune_batch(int32_t nitem, const rfi_batch_item* items, const rfi_
     // sums: tile variant x ring depth, then the XCD group size
     rfi_tune_entry best = cur;
     float best_ccm = ccm_def;
+    // (the instances that the defaults of these items run need no second timing)
     std::vector<long long> seen;
     {
-      rfi::CcmClass c0;
-      if (rfi::ccm_class(kv.second.empty() ? 19 : max_nbeam[sc], &c0, nullptr, 1 << 20, 1024, false) ==
-          hipSuccess)
-        seen.push_back(c0.key);
+      one.e[0] = cur;
+      rfi_batch_params q = base;
+      q.tune = &one;
+      rfi::BatchPlan bp;
+      if (rfi::plan_batch((int32_t)sub.size(), sub.data(), &q, &bp, who) == RFI_OK)
+        for (const rfi::CcmLaunchClass& c : bp.ccm_classes)
+          seen.push_back(bp.plans[c.items[0]].cc.key);
     }
     for (int tile = 0; tile < rfi::ccm_tile_variants(max_nbeam[sc]); ++tile) {
       for (int stages = 4; stages >= 2; --stages) {
@@ -627,8 +631,8 @@ rfi_status rfi_tune_batch(int32_t nitem, const rfi_batch_item* items, const rfi_
         e.ccm_tile = tile;
         e.ccm_stages = stages;
         rfi::CcmTune ct{tile, stages, 0};
-        rfi::CcmClass cc;
-        if (rfi::ccm_class(max_nbeam[sc], &cc, &ct, 1 << 20, 1024, false) != hipSuccess) continue;
+        rfi::CcmClass cc;   // whole blocks, whatever the size of the launch
+        if (rfi::ccm_class(max_nbeam[sc], &cc, &ct, 0, 0, false) != hipSuccess) continue;
         if (std::find(seen.begin(), seen.end(), cc.key) != seen.end()) continue;
         seen.push_back(cc.key);
         const float t = measure(e, 0, 4.f * best_ccm);

@@ -131,22 +131,25 @@ __device__ __forceinline__ void wait_chunk(int ahead) {
 }
 
 // Tiles per XCD group: 1 KB of contiguous row bytes by default (measured best
-// for the 4 KB-row FAST layout); a tune entry may choose another size.
-int group_tiles(int cw, int group_bytes_override = 0) {
+// for the 4 KB-row FAST layout); a tune entry may choose another size. n: the
+// workgroups they are dealt to. A launch of fewer than 8 G workgroups gets eight
+// groups of what it has: ungrouped, the tiles that share a 128-byte line are fetched
+// through all eight L2s (79 beams x 256 channels x 203450 samples, 256 workgroups of
+// 16 channels: 4643 us, grouped 2073).
+__host__ __device__ inline int group_tiles(int G, int64_t n) {
+  return (int64_t)8 * G > n ? (int)(n / 8) : G;
+}
+int group_tiles(int cw, int group_bytes_override, int64_t n) {
   const int gb = group_bytes_override > 0 ? group_bytes_override : 1024;
-  return gb / cw > 1 ? gb / cw : 1;
+  return group_tiles(gb / cw, n);
 }
 
 // workgroup -> tile: G consecutive channel tiles of a sub-interval (G CW
 // contiguous bytes of every row) go to G workgroups that are dispatched
 // back to back on the same XCD (workgroup ids w, w + 8, w + 16, ...): the
 // hardware dispatcher then keeps adjacent tiles in step, and each row is
-// fetched in long runs through one L2. A launch of fewer than 8 G workgroups gets
-// eight groups of what it has: ungrouped, the tiles that share a 128-byte line are
-// fetched through all eight L2s (79 beams x 256 channels x 203450 samples, 256
-// workgroups of 16 channels: 4643 us, grouped 2073).
+// fetched in long runs through one L2
 __device__ __forceinline__ int xcd_group(int w, int n, int G) {
-  G = min(G, n / 8);
   const int full = G > 1 ? (n / (8 * G)) * (8 * G) : 0;
   if (w >= full) return w;
   const int u = w / (8 * G), rem = w % (8 * G);
@@ -157,7 +160,8 @@ __device__ __forceinline__ int xcd_group(int w, int n, int G) {
 // workgroup each, the samples of the later ones are shared out to `parts`.
 // Sub-interval k, channel tile ct, samples [r0, r0 + n) of its L (whole chunks
 // of TC; n <= 0: more parts than this needs). A workgroup of parts > 1 adds its
-// sums to the outputs (zero before the launch, or the caller's).
+// sums to the outputs (zero before the launch, or the caller's). G: the group of
+// the whole tiles in the low half, of the shared ones in the high half.
 struct Tile {
   int k, ct, part, parts, r0, n;
 };
@@ -166,12 +170,12 @@ __device__ __forceinline__ Tile tile_of(int w, int ntiles, int nct, int nwhole, 
   Tile t;
   int tile;
   if (w < nwhole) {
-    tile = xcd_group(w, nwhole, G);
+    tile = xcd_group(w, nwhole, G & 0xffff);
     t.part = 0;
     t.parts = 1;
   } else {
     const int tail = ntiles - nwhole;
-    const int m = xcd_group(w - nwhole, tail * parts, G);
+    const int m = xcd_group(w - nwhole, tail * parts, G >> 16);
     tile = nwhole + m % tail;
     t.part = m / tail;
     t.parts = parts;
@@ -259,6 +263,7 @@ __global__ __launch_bounds__((MfmaCfg<NB, CW, CPW, IPW, NST>::NTHR), 1) void ccm
     w -= it.wg0;
     if (w >= nsub * nct * parts) return;      // padding to a multiple of 8 workgroups
     nwhole = 0;
+    G = group_tiles(G, nsub * nct * parts) << 16;
     kstride = 0;
     ksplit = 1;
     Llast = L;
@@ -623,6 +628,7 @@ __global__ __launch_bounds__((PackCfg<NBF, Q, ONES>::NTHR), NBF <= 2 ? 4 : 2) vo
     w -= it.wg0;
     if (w >= nsub * nct * parts) return;      // padding to a multiple of 8 workgroups
     nwhole = 0;
+    G = group_tiles(G, nsub * nct * parts) << 16;
     kstride = 0;
     ksplit = 1;
     Llast = L;
@@ -1090,15 +1096,17 @@ hipError_t launch_cfg(K kern, int nh, const BeamPtrs& bp, int nbeam, int nchan, 
                                      hipFuncAttributeMaxDynamicSharedMemorySize, C::LDS);
   if (e != hipSuccess) return e;
   const int64_t ntiles = (int64_t)nsub * nct;
-  const int G = group_tiles(C::WIDTH, group_bytes);
   const CcmShare sh = ksplit > 1 ? CcmShare{(int)ntiles, 1, 0}
                                  : ccm_share(ntiles, L, C::SLOTS, shared_epilogue<C>(nbeam));
+  const int64_t nshared = (ntiles - sh.nwhole) * sh.parts;
+  const int G = group_tiles(C::WIDTH, group_bytes, sh.nwhole) |
+                group_tiles(C::WIDTH, group_bytes, nshared) << 16;
   if (sh.parts > 1 && !accumulate) {
     e = launch_zero(sum_x, sum_xy, nbeam, (int64_t)nsub * nchan,
                     (int64_t)(sh.nwhole / nct) * nchan, layout, s);
     if (e != hipSuccess) return e;
   }
-  hipLaunchKernelGGL(kern, dim3((unsigned)(sh.nwhole + (ntiles - sh.nwhole) * sh.parts)),
+  hipLaunchKernelGGL(kern, dim3((unsigned)(sh.nwhole + nshared)),
                      dim3(C::NTHR), C::LDS, s, bp, nbeam, nchan, row_stride, t0, L, nsub, nct, sum_x,
                      sum_xy, count, accumulate, G, nh, layout, kstride, ksplit, Llast,
                      sh.nwhole, sh.parts, (const CcmItem*)nullptr, 0);
@@ -1111,7 +1119,7 @@ hipError_t launch_batch_cfg(K kern, const CcmItem* items, int nitem, int total_w
   hipError_t e = hipFuncSetAttribute((const void*)kern,
                                      hipFuncAttributeMaxDynamicSharedMemorySize, C::LDS);
   if (e != hipSuccess) return e;
-  const int G = group_tiles(C::WIDTH, group_bytes);
+  const int G = group_tiles(C::WIDTH, group_bytes, INT64_MAX);
   BeamPtrs none;
   memset(&none, 0, sizeof(none));
   hipLaunchKernelGGL(kern, dim3((unsigned)total_wg), dim3(C::NTHR), C::LDS, s, none, 0, 0,

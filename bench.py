@@ -743,7 +743,7 @@ def main():
             traffic = int(rec["traffic_bytes"])
     if ms_ccm >= ms_eig:
         ccm_gbs = nbytes_in / (ms_ccm / 1e3) / 1e9
-        roof = {"kernel": "ccm_pack_kernel (64-channel tiles, one launch per block)"
+        roof = {"kernel": "sums kernel (64-channel tiles, one launch per block)"
                           if variant == rfi.RFI_CCM_MFMA else "ccm_valu_kernel",
                 "bound": "hbm", "achieved": round(ccm_gbs, 1), "peak": HBM_PEAK_GBS,
                 "unit": "GB/s", "frac": round(ccm_gbs / HBM_PEAK_GBS, 4), "traffic": traffic,

@@ -213,8 +213,9 @@ rfi_status rfi_eig_batched_long(int32_t nbeam, int32_t nsub, int32_t nchan, cons
  * baseline, the bandpass to subtract from every sample of the channel;
  * passes[k nbeam + b] (nullable) the passes taken. Inputs in the rows layout
  * of rfi_ccm_accumulate. workspace: rfi_bandpass_workspace_size bytes
- * (caller-owned, one call at a time). One workgroup per (beam, sub-interval):
- * its threads reduce a chunk of channels each and share the rest of the solve.
+ * (caller-owned, one call at a time; read and written above 8192 channels only).
+ * One workgroup per (beam, sub-interval): its threads reduce a chunk of channels
+ * each and share the rest of the solve.
  * Errors: RFI_E_INVALID for bad sizes, lam <= 0, ratio < 0, itermax < 1 or
  * NULL pointers. */
 size_t rfi_bandpass_workspace_size(int32_t nbeam, int32_t nchan, int32_t nsub);
@@ -325,7 +326,12 @@ rfi_status rfi_flag_noalloc(int32_t nsub, int32_t nchan, const double* stat,
  * bins or c >= 0 keep the moment fit. Summaries (nullable): out for the
  * global scope, chan_out[nchan] per channel, sub_out[nsub] per sub-interval.
  * workspace: rfi_flag_workspace_size bytes (256-byte aligned) when the global
- * scope uses the moment fit, else unused (may be NULL).
+ * scope uses the moment fit, else unused (may be NULL). The global scope's
+ * histogram fit over more than 16384 cells keeps its state in the first bytes of
+ * mask until the mask itself is written (at most 16 KB, updated with device
+ * atomics): mask has to be plain device memory, and holds neither the old nor the
+ * new mask while the call runs. A mask that overlaps stat, status, protect_chan or
+ * out is not used so.
  * Errors: RFI_E_INVALID for bad sizes, scopes outside 1..7, an unknown fit,
  * kappa < 0, max_iter < 1 or a missing workspace. */
 enum { RFI_SCOPE_GLOBAL = 1, RFI_SCOPE_CHANNEL = 2, RFI_SCOPE_SUBINT = 4 };

@@ -38,7 +38,8 @@
 namespace rfi {
 namespace {
 
-constexpr int kVecs = 7;          // doubles of workspace per channel and system
+constexpr int kVecs = 7;          // doubles of workspace per channel and system (M = 0: six
+                                  // vectors of at most 7/6 of the channels; else unused)
 constexpr int kMinRows = 4;       // rows per chunk: at least two interior ones
 constexpr int kLdsVecs = 9;       // doubles per block of the reduced system
 
@@ -486,10 +487,14 @@ size_t bandpass_workspace_size(int nbeam, int nchan, int nsub) {
   return (size_t)kVecs * nchan * nbeam * nsub * sizeof(double);
 }
 
-// Chunks by channel count: up to 16 rows of a chunk fit the registers (six
-// vectors of FP64), so T = 64, 256 or 512 threads cover 8192 channels; one
-// wavefront suffices (and needs no barrier) up to 1024. Beyond, the vectors
-// live in the workspace (6 vectors of at most nchan + 511 <= 7/6 nchan rows).
+// Chunks by channel count: up to 16 rows of a chunk (six vectors of FP64) in
+// registers, so T = 64, 256 or 512 threads cover 8192 channels; one wavefront
+// suffices (and needs no barrier) up to 1024. At 512 threads (4097 channels and more)
+// a thread has 256 registers and 484 bytes a lane go to scratch inside the solve: 190
+// systems of 4096 / 4097 / 8192 channels 57 / 139 / 166 us (one thread per system and
+// a sequential Cholesky 9919 / 9901 / 19848). Beyond 8192 channels the vectors live in
+// the workspace (6 vectors of at most nchan + 511 <= 7/6 nchan rows): 8193 channels
+// 260 us.
 hipError_t launch_arpls(int nbeam, int nsub, int nchan, const int32_t* sum_x,
                         const int32_t* count, double lam, double ratio, int itermax, double* z,
                         int32_t* passes, void* ws, hipStream_t s) {

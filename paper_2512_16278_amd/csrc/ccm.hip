@@ -520,14 +520,20 @@ __global__ __launch_bounds__((MfmaCfg<NB, CW, CPW, IPW, NST>::NTHR), 1) void ccm
 // straight from the accumulators: staging them in LDS was a quarter of the launch
 // (36 beams measured better staged, 425 against 450 us). Bound: the memory system
 // at the piece size, then the epilogue. Whole blocks -> packed: 36 beams x 1000
-// channels x 1024 samples x 39 585 -> 425 us (3.4 TB/s); 72 x 1024 x 512 x 40 1019
-// -> 724 us; 19 x 4096 x 2048 x 99 3241 -> 3130 us (5.0 TB/s), x 1024 x 1017 x 60 277
-// -> 254 us.
+// channels x 1024 samples x 39 585 -> 425 us (3.4 TB/s); 19 x 4096 x 2048 x 99 3241
+// -> 3130 us (5.0 TB/s), x 1024 x 1017 x 60 277 -> 254 us; 72 x 1024 x 512 x 40 as
+// cell records 1019 -> 697 us, rows 1179 -> 980.
+// The instances of 64 beams and more overflow their 256 registers: 48 bytes of
+// scratch a lane up to 67 beams, 136 from 68 on, where one accumulator is stored and
+// reloaded in every K = 32 step. The reload waits for the loads of all stages ahead,
+// so the ring is empty when a step ends: 2.2 TB/s at 72 beams where bare 32-byte
+// pieces reach 3.6. (The extra operations make the counted waits wait longer, never
+// shorter.)
 //
 // A wave owns CPW channels and reads a row's CPW bytes of a beam in one LDS load;
 // 16-byte units are XOR-swizzled by the beam, which spreads the 16 beams of a
 // load over all banks. Load addresses are recomputed per stage from the beam
-// table (scalar loads), which keeps their registers free.
+// table (scalar loads), which leaves their registers to the accumulators.
 template <int NBF, int Q, bool ONES>
 struct PackCfg {
   static constexpr int TR = 16;                        // rows per stage

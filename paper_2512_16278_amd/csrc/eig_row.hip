@@ -28,9 +28,12 @@
 // instead of a reciprocal and three, rescaled every eight steps).
 //
 // Bound: FP64 instruction issue, at two to three wavefronts per SIMD. 36 beams,
-// 39000 cells with eigenvalues and vectors: 5290 -> 1196 us; 19 beams, raw
+// 39000 cells with eigenvalues and vectors: 5290 -> 1140 us; 19 beams, raw
 // moments, 40960 cells: 407 -> 117 us (before: one wavefront per cell with the
-// matrix on an 8 x 8 lane grid and the vectors in LDS).
+// matrix on an 8 x 8 lane grid and the vectors in LDS). Launches of a few hundred
+// cells are a wavefront's latency, and four cells to it are longer than one was: 256
+// cells of 37..40 beams (80 bytes of scratch) 43 -> 49 us, 33..36 41 -> 43, fewer as
+// before or faster.
 #include <math.h>
 
 #include "internal.h"

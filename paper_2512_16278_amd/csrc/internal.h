@@ -26,7 +26,7 @@ struct CcmItem {
   int32_t* count;
   int32_t nbeam, nchan, L, nsub;
   int32_t nct, nh, wg0, layout;  // layout: as the sums engine's argument
-  int32_t parts, pad;            // workgroups per tile (ccm_item_parts)
+  int32_t parts, pad;            // workgroups per tile (plan_parts in batch.cpp)
 };
 // Launch choices of the MFMA sums engine (all 0 = defaults): tile = variant
 // index of the beam count's tile shapes (< ccm_tile_variants), stages = cap

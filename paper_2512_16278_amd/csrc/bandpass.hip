@@ -254,7 +254,8 @@ __global__ __launch_bounds__(T) void arpls_kernel(BpArgs a) {
     }
     __syncthreads();
     // the levels over nb blocks. At full width nb is the constant T and the loops over
-    // the levels unroll (190 systems of 256 channels 25 us, 27 us with nb = Tn alone)
+    // the levels unroll (190 systems of 256 channels 25 us, 27 us with nb = Tn alone);
+    // 512 threads have no registers left for that (9000 channels 179 us rolled, 192)
     auto solve_reduced = [&](const int nb) __attribute__((always_inline)) {
       // reduction: the odd blocks of a level survive, each absorbing its two
       // even neighbours
@@ -337,7 +338,7 @@ __global__ __launch_bounds__(T) void arpls_kernel(BpArgs a) {
         __syncthreads();
       }
     };
-    if (Tn == T)
+    if (T < 512 && Tn == T)
       solve_reduced(T);
     else
       solve_reduced(Tn);

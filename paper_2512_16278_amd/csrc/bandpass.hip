@@ -22,14 +22,14 @@
 //    levels of cyclic reduction (every second block eliminated per level) and
 //    solved back the same way;
 //  - each thread substitutes back inside its chunk;
-//  - after the last pass one more solve, of that pass's residual, takes the
-//    rounding of the elimination out of z (error against an extended-precision
-//    solve 4.3e-12 of the spectrum, 7.7e-12 without; a sequential FP64 Cholesky
-//    has 6.4e-12).
+//  - after the last pass (after every pass for a large lam) one more solve, of
+//    that pass's residual, takes the rounding of the elimination out of z (error
+//    against an extended-precision solve 4.3e-12 of the spectrum, 7.7e-12
+//    without; a sequential FP64 Cholesky has 6.4e-12).
 // Rows past the last channel are unit rows (w = 1, y = 0, no coupling).
 // Bound: latency of the dependent FP64 steps (one reciprocal per row of a
-// chunk, log2 T levels each way). 190 systems of 4096 channels: 54 us, against
-// 6842 us with one thread per system and a sequential Cholesky.
+// chunk, log2 T levels each way). 190 systems of 4096 channels, two passes: 44 us,
+// against 6811 us with one thread per system and a sequential Cholesky.
 #include <hip/hip_runtime.h>
 #include <math.h>
 
@@ -42,6 +42,7 @@ constexpr int kVecs = 7;          // doubles of workspace per channel and system
                                   // vectors of at most 7/6 of the channels; else unused)
 constexpr int kMinRows = 4;       // rows per chunk: at least two interior ones
 constexpr int kLdsVecs = 9;       // doubles per block of the reduced system
+constexpr double kRefineLam = 1e6;   // from here on every pass is refined: see launch_arpls
 
 struct BpArgs {
   int nbeam, nsub, nchan, itermax;
@@ -129,7 +130,8 @@ struct Sym2 {
 // reading consecutive chunks do not meet in one bank
 __device__ __forceinline__ int pos(int j) { return j + (j >> 4); }
 
-template <int T, int M>
+// R: every pass's z is refined, not only the last one's
+template <int T, int M, bool R>
 __global__ __launch_bounds__(T) void arpls_kernel(BpArgs a) {
   extern __shared__ __attribute__((aligned(16))) double lds[];
   __shared__ double red[T / 64];
@@ -164,7 +166,10 @@ __global__ __launch_bounds__(T) void arpls_kernel(BpArgs a) {
     for (int i = 0; i < m; ++i) y[i] = s0 + i < F ? (double)sx[s0 + i] / L : 0.0;
   }
 #pragma unroll
-  for (int i = 0; i < m; ++i) w[i] = 1.0;
+  for (int i = 0; i < m; ++i) {
+    w[i] = 1.0;
+    x[i] = y[i];
+  }
 
   // reduced system, level by level: level l has Tn >> l blocks at offset
   // 2 Tn - (2 Tn >> l); arrays A (3: a, b, d), E (4: coupling to the block
@@ -177,10 +182,10 @@ __global__ __launch_bounds__(T) void arpls_kernel(BpArgs a) {
   double *Aa = arr(0), *Ab = arr(1), *Ad = arr(2), *E0 = arr(3), *E1 = arr(4), *E2 = arr(5),
          *E3 = arr(6), *R0 = arr(7), *R1 = arr(8);
 
-  // solves A x = rhs with rhs = W y, then (done) once more for the rounding of
-  // the last pass: rhs = its residual, held in y
+  // solves A x = rhs, rhs given in x: W y, or (fix) the residual of the solution
+  // before, which takes that one's rounding out
   int passes = 0;
-  bool done = false;
+  bool fix = false;
   for (;;) {
     __syncthreads();     // the staged spectrum / the last pass's solution has been read
     // coupling of this chunk's first two rows to the two rows before it
@@ -199,7 +204,7 @@ __global__ __launch_bounds__(T) void arpls_kernel(BpArgs a) {
       const double B = fma(-l1p, cpv, a.lam * c.d1);
       const double f = fma(-l2q, fq, fma(-l1p, fp, i == 0 ? f0 : 0.0));
       const double g = fma(-l2q, gq, fma(-l1p, gp, i == 0 ? g0 : (i == 1 ? g1 : 0.0)));
-      const double u = fma(-l2q, uq, fma(-l1p, up, done ? y[i] : w[i] * y[i]));
+      const double u = fma(-l2q, uq, fma(-l1p, up, x[i]));
       const double inv = rcp2(D);
       l1[i] = B * inv;
       l2[i] = cc * inv;
@@ -234,8 +239,8 @@ __global__ __launch_bounds__(T) void arpls_kernel(BpArgs a) {
       E1[t] = fma(-l2q, gq, -l1p * gp);
       E2[t] = -l2p * fp;
       E3[t] = -l2p * gp;
-      R0[t] = fma(-l2q, uq, fma(-l1p, up, done ? y[m - 2] : w[m - 2] * y[m - 2]));
-      R1[t] = fma(-l2p, up, done ? y[m - 1] : w[m - 1] * y[m - 1]);
+      R0[t] = fma(-l2q, uq, fma(-l1p, up, x[m - 2]));
+      R1[t] = fma(-l2p, up, x[m - 1]);
       // what eliminating this chunk adds to the block before it: kept in the
       // next level's space until that block has taken it
       Aa[T + t] = Spp;
@@ -348,7 +353,7 @@ __global__ __launch_bounds__(T) void arpls_kernel(BpArgs a) {
     double la = 0.0, lb = 0.0, lc = 0.0;               // l1[i-1], l2[i-2], l2[i-1]
 #pragma unroll
     for (int i = 0; i < m - 2; ++i) {
-      double rhs = done ? y[i] : w[i] * y[i];
+      double rhs = x[i];
       if (i == 0) rhs -= fma(f0, zp, g0 * zq);
       if (i == 1) rhs -= g1 * zq;
       const double u = fma(-lb, u2, fma(-la, u1, rhs));
@@ -369,63 +374,72 @@ __global__ __launch_bounds__(T) void arpls_kernel(BpArgs a) {
       z2 = z1;
       z1 = zi;
     }
-    if (done) break;
-    ++passes;
-    const bool last = passes == a.itermax;
-    // negative residuals: mean and sample standard deviation
-    double sn = 0.0, cnt = 0.0;
-#pragma unroll
-    for (int i = 0; i < m; ++i) {
-      const double d = y[i] - x[i];
-      if (s0 + i < F && d < 0.0) {
-        sn += d;
-        cnt += 1.0;
-      }
-    }
-    sn = bp_sum<T>(sn, red);
-    cnt = bp_sum<T>(cnt, red);
-    const double mean = sn / cnt;
-    double ss = 0.0;
-#pragma unroll
-    for (int i = 0; i < m; ++i) {
-      const double d = y[i] - x[i];
-      if (s0 + i < F && d < 0.0) ss = fma(d - mean, d - mean, ss);
-    }
-    ss = bp_sum<T>(ss, red);
-    const double sd = sqrt(ss / (cnt - 1.0));
-    bool stop = cnt < 2.0 || !(sd > 0.0);
-    if (!stop && !last) {
-      // new weights (over l1, free until the next solve), kept until the test
-      double dw = 0.0, nw = 0.0;
+    if constexpr (R) {
+      if (fix) {
 #pragma unroll kU
+        for (int i = 0; i < m; ++i) x[i] += zo[s0 + i < F ? s0 + i : F - 1];
+      }
+    } else if (fix) {
+      break;
+    }
+    if (fix || !R) {
+      ++passes;
+      const bool last = passes == a.itermax;
+      // negative residuals: mean and sample standard deviation
+      double sn = 0.0, cnt = 0.0;
+#pragma unroll
       for (int i = 0; i < m; ++i) {
         const double d = y[i] - x[i];
-        const double wt = 1.0 / (1.0 + exp(2.0 * (d - (2.0 * sd - mean)) / sd));
-        const double wo = w[i];
-        if (s0 + i < F) {
-          dw = fma(wo - wt, wo - wt, dw);
-          nw = fma(wo, wo, nw);
-          l1[i] = wt;
-        } else {
-          l1[i] = 1.0;
+        if (s0 + i < F && d < 0.0) {
+          sn += d;
+          cnt += 1.0;
         }
       }
-      dw = bp_sum<T>(dw, red);
-      nw = bp_sum<T>(nw, red);
-      stop = sqrt(dw) / sqrt(nw) < a.ratio;
-    }
-    if (!stop && !last) {
-      if constexpr (M > 0) {
+      sn = bp_sum<T>(sn, red);
+      cnt = bp_sum<T>(cnt, red);
+      const double mean = sn / cnt;
+      double ss = 0.0;
 #pragma unroll
-        for (int i = 0; i < M; ++i) w[i] = l1[i];
-      } else {
-#pragma unroll 1
-        for (int i = 0; i < m; ++i) w[i] = l1[i];
+      for (int i = 0; i < m; ++i) {
+        const double d = y[i] - x[i];
+        if (s0 + i < F && d < 0.0) ss = fma(d - mean, d - mean, ss);
       }
-      continue;
+      ss = bp_sum<T>(ss, red);
+      const double sd = sqrt(ss / (cnt - 1.0));
+      bool stop = cnt < 2.0 || !(sd > 0.0);
+      if (!stop && !last) {
+        // new weights (over l1, free until the next solve), kept until the test
+        double dw = 0.0, nw = 0.0;
+#pragma unroll kU
+        for (int i = 0; i < m; ++i) {
+          const double d = y[i] - x[i];
+          const double wt = 1.0 / (1.0 + exp(2.0 * (d - (2.0 * sd - mean)) / sd));
+          const double wo = w[i];
+          if (s0 + i < F) {
+            dw = fma(wo - wt, wo - wt, dw);
+            nw = fma(wo, wo, nw);
+            l1[i] = wt;
+          } else {
+            l1[i] = 1.0;
+          }
+        }
+        dw = bp_sum<T>(dw, red);
+        nw = bp_sum<T>(nw, red);
+        stop = sqrt(dw) / sqrt(nw) < a.ratio;
+      }
+      if (!stop && !last) {
+#pragma unroll kU
+        for (int i = 0; i < m; ++i) {
+          w[i] = l1[i];
+          x[i] = w[i] * y[i];
+        }
+        fix = false;
+        continue;
+      }
+      if constexpr (R) break;
     }
-    // the last pass: z goes out, and its residual W (y - z) - lam D^T (D z)
-    // replaces y. The differences of neighbouring z are exact or nearly so, so
+    // z goes out, and its residual W (y - z) - lam D^T (D z) is the next
+    // right-hand side. The differences of neighbouring z are exact or nearly so, so
     // the residual is accurate far below the rounding of the solve and one more
     // solve takes that rounding out of z.
     __syncthreads();                      // the reduced system is read no more
@@ -451,38 +465,37 @@ __global__ __launch_bounds__(T) void arpls_kernel(BpArgs a) {
     for (int i = 0; i < m; ++i) {
       const double e0 = d_at(s0 + i);
       const double res = fma(-a.lam, (e0 - e1) - (e1 - e2), w[i] * (y[i] - x[i]));
-      y[i] = s0 + i < F ? res : 0.0;
+      x[i] = s0 + i < F ? res : 0.0;
       e2 = e1;
       e1 = e0;
     }
     if constexpr (M > 0) {
       for (int j = t; j < F; j += T) zo[j] = lds[pos(j)];
     }
-    done = true;
+    fix = true;
   }
-  // z plus its correction
   __syncthreads();
   if constexpr (M > 0) {
 #pragma unroll
     for (int i = 0; i < M; ++i)
       if (s0 + i < F) lds[pos(s0 + i)] = x[i];
     __syncthreads();
-    for (int j = t; j < F; j += T) zo[j] += lds[pos(j)];
+    for (int j = t; j < F; j += T) zo[j] = R ? lds[pos(j)] : zo[j] + lds[pos(j)];
   } else {
     for (int i = 0; i < m; ++i)
-      if (s0 + i < F) zo[s0 + i] += x[i];
+      if (s0 + i < F) zo[s0 + i] = R ? x[i] : zo[s0 + i] + x[i];
   }
   if (a.passes && t == 0) a.passes[k * a.nbeam + b] = passes;
 }
 
-template <int T, int M>
+template <int T, int M, bool R>
 hipError_t launch_bp(BpArgs a, int nsys, hipStream_t s) {
   a.m = M ? M : (a.nchan + T - 1) / T;
   if (a.m < kMinRows) a.m = kMinRows;
   size_t shm = (size_t)kLdsVecs * 2 * T * sizeof(double);
   const size_t stage = (size_t)(T * M + T * M / 16 + 1) * sizeof(double);
   if (M && stage > shm) shm = stage;
-  const auto kern = arpls_kernel<T, M>;
+  const auto kern = arpls_kernel<T, M, R>;
   hipError_t e = hipFuncSetAttribute((const void*)kern,
                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)shm);
   if (e != hipSuccess) return e;
@@ -499,23 +512,37 @@ size_t bandpass_workspace_size(int nbeam, int nchan, int nsub) {
 // Chunks by channel count: up to 16 rows of a chunk (six vectors of FP64) in
 // registers, so T = 64, 256 or 512 threads cover 8192 channels; one wavefront
 // suffices (and needs no barrier) up to 1024. At 512 threads (4097 channels and more)
-// a thread has 256 registers and 484 bytes a lane go to scratch inside the solve: 190
-// systems of 4096 / 4097 / 8192 channels 57 / 139 / 166 us (one thread per system and
-// a sequential Cholesky 9919 / 9901 / 19848). Beyond 8192 channels the vectors live in
-// the workspace (6 vectors of at most nchan + 511 <= 7/6 nchan rows): 8193 channels
-// 260 us.
+// a thread has 256 registers and 488 bytes a lane go to scratch inside the solve: 190
+// systems of 4096 / 4097 / 8192 channels, two passes, 44 / 96 / 105 us (one thread per
+// system and a sequential Cholesky 6811 / 6786 / 13643). Beyond 8192 channels the
+// vectors live in the workspace (6 vectors of at most nchan + 511 <= 7/6 nchan rows):
+// 8193 channels 178 us (13573).
+template <bool R>
+hipError_t launch_sized(const BpArgs& a, int nsys, hipStream_t s) {
+  if (a.nchan <= 64 * 4) return launch_bp<64, 4, R>(a, nsys, s);
+  if (a.nchan <= 64 * 16) return launch_bp<64, 16, R>(a, nsys, s);
+  if (a.nchan <= 256 * 8) return launch_bp<256, 8, R>(a, nsys, s);
+  if (a.nchan <= 256 * 16) return launch_bp<256, 16, R>(a, nsys, s);
+  if (a.nchan <= 512 * 16) return launch_bp<512, 16, R>(a, nsys, s);
+  return launch_bp<512, 0, R>(a, nsys, s);
+}
+
+// The rounding of a solve grows with lam (condition number about 16 lam / the smallest
+// weight), enters the next pass through the weights and is not taken out by a last
+// solve alone: with only the last pass refined, 38 systems of 1024 channels at lam =
+// 1e9 were 2.5e-5 off (median 1.4e-5) against 7.8e-6 (3.5e-6) of one sequential FP64
+// Cholesky per pass; at 1e7, 256 channels 8.4e-8 (median) against 5.8e-8; at the default
+// 1e5 it is the more accurate one (median 3.9e-10 against 1.1e-9), and at 1e6 still
+// (2.6e-9 against 8.2e-9). With every pass refined 4.3e-9 (1.3e-9) at 1e9, for up to
+// twice the solves: 13 passes of 1024 channels 222 us instead of 135 (the Cholesky
+// 10433).
 hipError_t launch_arpls(int nbeam, int nsub, int nchan, const int32_t* sum_x,
                         const int32_t* count, double lam, double ratio, int itermax, double* z,
                         int32_t* passes, void* ws, hipStream_t s) {
   const int nsys = nbeam * nsub;
   if (nsys == 0) return hipSuccess;
   BpArgs a{nbeam, nsub, nchan, itermax, 0, lam, ratio, sum_x, count, z, passes, (double*)ws};
-  if (nchan <= 64 * 4) return launch_bp<64, 4>(a, nsys, s);
-  if (nchan <= 64 * 16) return launch_bp<64, 16>(a, nsys, s);
-  if (nchan <= 256 * 8) return launch_bp<256, 8>(a, nsys, s);
-  if (nchan <= 256 * 16) return launch_bp<256, 16>(a, nsys, s);
-  if (nchan <= 512 * 16) return launch_bp<512, 16>(a, nsys, s);
-  return launch_bp<512, 0>(a, nsys, s);
+  return lam >= kRefineLam ? launch_sized<true>(a, nsys, s) : launch_sized<false>(a, nsys, s);
 }
 
 }  // namespace rfi

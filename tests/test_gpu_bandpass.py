@@ -130,6 +130,75 @@ def test_arpls_chunk_edges(dev, F):
             assert pg[k, b] == n
 
 
+def _arpls_extended(y, lam, ratio, itermax):
+    """ArPLS of the rows of y in extended precision (LDL^T along the channels), each pass's
+    solution refined once with its residual."""
+    ld = np.longdouble
+    n, F = y.shape
+    d0, d1, d2 = (np.zeros(F, ld) for _ in range(3))
+    for r in range(F - 2):
+        d0[r:r + 3] += (1, 4, 1)
+        d1[r:r + 2] += (-2, -2)
+        d2[r] += 1
+
+    def solve(w, rhs):
+        e1, e2 = np.zeros((F, n), ld), np.zeros((F, n), ld)     # L's sub-diagonals, by column
+        D, u = (w + lam * d0).T.copy(), rhs.T.copy()
+        for j in range(F):
+            if j >= 2:
+                D[j] -= e2[j - 2] ** 2 * D[j - 2]
+                u[j] -= e2[j - 2] * u[j - 2]
+            if j >= 1:
+                c = lam * d1[j - 1] - (e1[j - 2] * e2[j - 2] * D[j - 2] if j >= 2 else 0)
+                e1[j - 1] = c / D[j - 1]
+                D[j] -= e1[j - 1] * c
+                u[j] -= e1[j - 1] * u[j - 1]
+            e2[j] = lam * d2[j] / D[j]
+        z = np.zeros((F + 2, n), ld)
+        for j in range(F - 1, -1, -1):
+            z[j] = u[j] / D[j] - e1[j] * z[j + 1] - e2[j] * z[j + 2]
+        return z[:F].T.copy()
+
+    w, z, passes = np.ones_like(y), y.copy(), np.zeros(n, int)
+    todo = np.ones(n, bool)
+    while todo.any() and passes.max() < itermax:
+        zt = solve(w, w * y)
+        zz = np.diff(zt, 2, axis=1)                             # D z
+        g = np.pad(zz, ((0, 0), (2, 2)))
+        zt += solve(w, w * (y - zt) - lam * np.diff(g, 2, axis=1))
+        z[todo] = zt[todo]
+        passes[todo] += 1
+        for i in np.flatnonzero(todo):
+            d = y[i] - z[i]
+            neg = d[d < 0]
+            m, s = neg.mean(), neg.std(ddof=1)
+            wt = 1 / (1 + np.exp(2 * (d - (2 * s - m)) / s))
+            if np.linalg.norm(w[i] - wt) / np.linalg.norm(w[i]) < ratio:
+                todo[i] = False
+            w[i] = wt
+    return z, passes
+
+
+@pytest.mark.parametrize("F", [16, 256, 1000, 1024, 2000, 4096, 4500, 8193])
+def test_arpls_stiff(dev, F):
+    """A large lam, where a pass's rounding enters the next one's weights. One FP64 solve is off
+    by up to k u of the spectrum's scale: u = 1.1e-16, k = 16 lam / 0.1 = 1.6e11, the weights
+    averaging at least 0.1 here; refined in every pass, by (k u)^2, and ten times that for the
+    way through the passes: 3e-9 of the scale (a sequential FP64 Cholesky is 3e-8 to 3e-7
+    off)."""
+    rng = np.random.default_rng(F)
+    lam, nb = 1e9, 6
+    j = np.arange(F)
+    y = 60 + 30 * np.sin(2 * np.pi * j / F)[None, :] + rng.standard_normal((nb, F))
+    y[:, ::37] += 30
+    S = np.rint(y * 1000).astype(np.int64).T[None]
+    zg, pg = _run_arpls(dev, S, np.array([1000]), lam=lam)
+    ze, pe = _arpls_extended(S[0].T.astype(np.longdouble) / 1000, lam, 0.05, 100)
+    tol = 10 * (1.6e11 * 2.0 ** -53) ** 2
+    assert np.abs(zg[0].T - ze).max() <= tol * np.abs(y).max()
+    assert np.array_equal(pg[0], pe)
+
+
 def test_arpls_edge_cases(dev):
     rng = np.random.default_rng(5)
     # fewer than three channels: the baseline is the spectrum itself
